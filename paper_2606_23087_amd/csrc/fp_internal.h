@@ -149,26 +149,48 @@ struct Divisors {
   int32_t div_shift, pt_shift, pb_shift;
 };
 
-// Workgroups of one producer write at most; a larger write loops over its
-// chunks. (Smaller caps, 128 to 512, made writes slower and did not make the
-// packs beside them measurably faster.)
-constexpr int kWriteGrid = 1 << 16;
-
 // The producer's write of one sample: its visual rows (contiguous at `vis`)
-// are copied into its pages in chunks of kChunkVecs vectors, like a pack
-// with source and destination exchanged.
-struct WriteArgs {
+// are copied into its pages, cut into chunks like a pack, and its metadata
+// (page list, image list, text ids) and descriptor go from pinned host memory
+// and the kernel arguments into the arena, in one launch. The numbers of up to
+// kInlinePages scattered pages travel in the arguments (WriteArgs); of
+// consecutive pages the first alone does, and a longer scattered list is read
+// from the staging buffer (both WriteArgsSmall).
+template <int kCapacity>
+struct WriteArgsT {
   SampleDesc desc;            // descriptor to publish into the table
   SampleDesc* desc_table;
-  int32_t slot;
-  int32_t row_bytes;
-  const uint8_t* meta;
+  const uint8_t* stage;       // the metadata block in pinned host memory (16-byte aligned)
+  uint8_t* meta;              // where it goes in the device arena
   const uint64_t* pte;
-  uint64_t gva_start;
-  const uint8_t* vis;         // producer rows, or null
+  int32_t slot;
+  int32_t meta_vecs;          // 16-byte vectors of the metadata block
+  int32_t row_bytes;
   int32_t page_tokens;
+  int32_t staged_pages;       // WriteArgsSmall: page GVAs are the block's first words, else consecutive
+  uint64_t gva_start;
+  uint64_t pt_mul, pb_mul;    // division constants (as in PackArgs)
+  int32_t pt_shift, pb_shift;
+  uint32_t page[kCapacity];   // page numbers (WriteArgsSmall: of page 0)
+  static constexpr int kPages = kCapacity;
+};
+// Kernel arguments cost host time by their size (a launch measured 2.5 us
+// with 64 bytes of them, 3.5 with 512, 4.7 with 1024), so writes whose page
+// numbers need no list take the small form.
+constexpr int kInlinePages = 192;
+using WriteArgs = WriteArgsT<kInlinePages>;
+using WriteArgsSmall = WriteArgsT<1>;
+static_assert(offsetof(WriteArgs, page) == offsetof(WriteArgsSmall, page), "same scalar fields");
+// Metadata vectors one workgroup of a write uploads.
+constexpr int kMetaVecs = kPackBlock * 4;
+
+struct WritePlan {
+  WriteArgs a;
+  const uint8_t* vis;         // producer rows, or null
+  bool inline_pages;          // launch with WriteArgs, else WriteArgsSmall
   int32_t max_chunk_rows;     // rows one chunk can touch
-  Divisors dv;
+  uint64_t div_mul;           // e / (row_bytes/16) == (e * div_mul) >> div_shift
+  int32_t div_shift;
 };
 
 size_t pack_lds_bytes(const PackPlan& pl);
@@ -176,7 +198,8 @@ Divisors make_divisors(int64_t row_bytes, int64_t page_tokens, uint64_t page_byt
 // Chunk geometry of a pack (g0, g1, t1, t2) for a device with n_cu compute units.
 void pack_chunks(PackPlan* pl, int n_cu);
 hipError_t launch_pack(const PackPlan& pl, hipStream_t stream);
-hipError_t launch_write(const WriteArgs& a, hipStream_t stream);
+// Launches a write; `done` completes with its kernel.
+hipError_t launch_write(const WritePlan& pl, int n_cu, hipStream_t stream, hipEvent_t done);
 // Measurement aids with the pack's geometry: a plain copy of `vecs` 16-byte
 // vectors (chunks sized as for rows of row_bytes), and a gather of n_rows
 // rows of row_bytes from the device addresses rows_src[] into consecutive

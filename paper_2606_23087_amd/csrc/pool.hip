@@ -157,7 +157,9 @@ struct RangeAlloc {
   }
 };
 
-// Pinned host buffer + device buffer + completion event, reused round-robin.
+// Pinned host buffer + device buffer, reused round-robin once the work that
+// reads them has completed: an event of its own, or (shared >= 0) one of the
+// pool's, of which the stage holds a reference.
 struct Stage {
   uint8_t* host = nullptr;
   uint8_t* host_dev = nullptr;   // the same pinned buffer as the GPU addresses it
@@ -166,6 +168,7 @@ struct Stage {
   size_t dev_cap = 0;
   hipEvent_t ev = nullptr;
   bool pending = false;
+  int32_t shared = -1;
 };
 
 struct SampleRec {
@@ -312,6 +315,11 @@ fp_status stage_acquire(fp_pool* p, size_t host_bytes, size_t dev_bytes, Stage**
     FP_HIP(hipEventSynchronize(s.ev));
     s.pending = false;
   }
+  if (s.shared >= 0) {
+    FP_HIP(hipEventSynchronize(p->events.ev[(size_t)s.shared]));
+    p->events.unref(s.shared);
+    s.shared = -1;
+  }
   if (host_bytes > s.host_cap) {
     if (s.host) FP_HIP(hipHostFree(s.host));
     s.host = nullptr;
@@ -420,6 +428,16 @@ void release_pages(fp_pool* p, const std::vector<uint64_t>& pages) {
     p->n_free[t] += 1;
     if (p->cfg.alloc_policy == FP_ALLOC_SCATTER) p->stack[t].push_back(i);
   }
+}
+
+// The page number (index into the page table) of a GVA.
+int64_t page_number(const fp_pool* p, uint64_t gva) { return (int64_t)((gva - p->gva_start) / (uint64_t)p->pb); }
+
+// True when a sample's pages have consecutive GVAs (a contiguous allocation).
+bool consecutive(const fp_pool* p, const std::vector<uint64_t>& pages) {
+  for (size_t k = 1; k < pages.size(); ++k)
+    if (pages[k] != pages[0] + k * (uint64_t)p->pb) return false;
+  return !pages.empty();
 }
 
 // Returns what a deferred free holds to the allocators.
@@ -875,8 +893,11 @@ fp_status pool_write_sample(fp_pool* p, const int32_t* text_ids, int32_t n_text,
     d.page_off = meta_off;
     d.img_off = meta_off + align16(8 * n_pages);
     d.text_off = d.img_off + align16(8ll * n_img);
+    // The write kernel reads the metadata from the pinned staging buffer, so
+    // nothing else is enqueued, and its completion is both the sample's write
+    // event and the staging buffer's.
+    Stage* s = nullptr;
     if (meta_len > 0) {
-      Stage* s = nullptr;
       st = stage_acquire(p, (size_t)meta_len, 0, &s);
       if (st != FP_OK) return rollback(st);
       std::memcpy(s->host, rec.pages.data(), 8 * (size_t)n_pages);
@@ -886,35 +907,50 @@ fp_status pool_write_sample(fp_pool* p, const int32_t* text_ids, int32_t n_text,
         img[2 * j + 1] = img_ntok[j];
       }
       if (n_text) std::memcpy(s->host + (d.text_off - meta_off), text_ids, 4 * (size_t)n_text);
-      hipError_t e = hipMemcpyAsync(p->meta_dev + meta_off, s->host, (size_t)meta_len,
-                                    hipMemcpyHostToDevice, hs);
-      if (e != hipSuccess) return rollback(fail(FP_EHIP, "metadata upload: %s", hipGetErrorString(e)));
-      st = stage_release(s, hs);
-      if (st != FP_OK) return rollback(st);
     }
     const int32_t slot = p->free_slots.back();
-    fp::WriteArgs wa{};
+    fp::WritePlan w;
+    fp::WriteArgs& wa = w.a;
     wa.desc = d;
     wa.desc_table = p->desc_dev;
-    wa.slot = slot;
-    wa.meta = p->meta_dev;
+    wa.stage = s ? s->host_dev : nullptr;
+    wa.meta = p->meta_dev + meta_off;
     wa.pte = p->pte_dev;
-    wa.gva_start = p->gva_start;
-    wa.vis = vis_dev;
+    w.vis = vis_dev;
+    wa.slot = slot;
+    wa.meta_vecs = (int32_t)(meta_len / 16);
     wa.row_bytes = (int32_t)p->rb;
     wa.page_tokens = p->cfg.page_tokens;
-    wa.max_chunk_rows = (int32_t)std::min<int64_t>(n_vis, fp::kChunkVecs / (p->rb / 16) + 2);
-    wa.dv = p->dv;
-    hipError_t e = fp::launch_write(wa, hs);
-    if (e != hipSuccess) return rollback(fail(FP_EHIP, "write kernel: %s", hipGetErrorString(e)));
+    wa.gva_start = p->gva_start;
+    wa.pt_mul = p->dv.pt_mul;
+    wa.pb_mul = p->dv.pb_mul;
+    wa.pt_shift = p->dv.pt_shift;
+    wa.pb_shift = p->dv.pb_shift;
+    wa.staged_pages = 0;
+    wa.page[0] = 0;
+    w.inline_pages = false;
+    if (consecutive(p, rec.pages)) {
+      wa.page[0] = (uint32_t)page_number(p, rec.pages[0]);
+    } else if (n_pages > fp::kInlinePages) {
+      wa.staged_pages = 1;
+    } else {
+      w.inline_pages = n_pages > 0;
+      for (int64_t k = 0; k < n_pages; ++k) wa.page[k] = (uint32_t)page_number(p, rec.pages[(size_t)k]);
+    }
+    w.max_chunk_rows = (int32_t)std::min<int64_t>(n_vis, fp::kChunkVecs / (p->rb / 16) + 2);
+    w.div_mul = p->dv.div_mul;
+    w.div_shift = p->dv.div_shift;
     int32_t ev = -1;
-    e = p->events.acquire(&ev);
-    if (e == hipSuccess) e = hipEventRecord(p->events.ev[(size_t)ev], hs);
+    hipError_t e = p->events.acquire(&ev);
+    if (e != hipSuccess) return rollback(fail(FP_EHIP, "write event: %s", hipGetErrorString(e)));
+    e = fp::launch_write(w, p->n_cu, hs, p->events.ev[(size_t)ev]);
     if (e != hipSuccess) {
-      // The write is already queued: wait for it rather than hand out its pages again.
-      (void)hipStreamSynchronize(hs);
-      if (ev >= 0) p->events.unref(ev);
-      return rollback(fail(FP_EHIP, "write event: %s", hipGetErrorString(e)));
+      p->events.unref(ev);
+      return rollback(fail(FP_EHIP, "write kernel: %s", hipGetErrorString(e)));
+    }
+    if (s) {
+      p->events.ref(ev);
+      s->shared = ev;
     }
     rec.written = ev;
     rec.write_stream = stream;
@@ -1395,14 +1431,9 @@ fp_status plan_pool_packing(fp_pool* p, const uint64_t* sample_ids, int32_t n, i
 // the shortcut: same-machine A/B, qwen (H 3584) 0.45 % faster per launch,
 // video (H 5120, 8 KiB chunks) 0.3 % slower with it.
 static int32_t image_word(const fp_pool* p, const SampleRec& r) {
-  const size_t n = r.pages.size();
-  if (n > 0 && p->rb < fp::kSmallChunkRowBytes) {
-    const uint64_t pb = (uint64_t)p->pb;
-    const uint64_t first = r.pages[0];
-    bool consecutive = true;
-    for (size_t k = 1; k < n && consecutive; ++k) consecutive = r.pages[k] == first + k * pb;
-    const int64_t vpn0 = (int64_t)((first - p->gva_start) / pb);
-    if (consecutive && vpn0 + (int64_t)n < INT32_MAX) return (int32_t)(-1 - vpn0);
+  if (p->rb < fp::kSmallChunkRowBytes && consecutive(p, r.pages)) {
+    const int64_t vpn0 = page_number(p, r.pages[0]);
+    if (vpn0 + (int64_t)r.pages.size() < INT32_MAX) return (int32_t)(-1 - vpn0);
   }
   return (int32_t)(r.page_off / 8);
 }
