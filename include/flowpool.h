@@ -38,10 +38,10 @@
  *  - Calls from several threads are serialised internally by a mutex, so a
  *    producer thread and a consumer thread may share one pool.
  *  - HIP graphs: pack_microbatch may be captured on a capturing stream when
- *    its row table travels in the kernel arguments (at most 32 samples whose
- *    rows form at most 160 runs, a run being a stretch of one sample's text
- *    rows, or of its image rows with no text row between them) and its
- *    samples' writes are known complete (a pack, plan or pool_reclaim after they finished has seen
+ *    it has at most 32 samples whose rows form at most 160 runs (a run being
+ *    a stretch of one sample's text rows, or of its image rows with no text
+ *    row between them), so that its row table travels in the kernel
+ *    arguments, and its samples' writes are known complete (a pack, plan or pool_reclaim after they finished has seen
  *    them; the capture makes no event queries); each replay packs the same
  *    samples into the same buffers, through the page lists they had at
  *    capture. A captured pack therefore holds its samples: pool_free_sample
@@ -376,7 +376,8 @@ fp_status plan_pool_packing(fp_pool* p, const uint64_t* sample_ids, int32_t n, i
  *                    copies rows on host-tier pages; FP_TIER_MASK_ALL both.
  *                    Two launches with the two masks write what one ALL does.
  * Asynchronous on `stream`. Duplicated ids are packed twice. The row table
- * travels in the kernel arguments for up to 32 samples and 160 runs; a larger
+ * travels in the kernel arguments while its 4 bytes a sample, 16 a run and at
+ * least 288 of index fit 3840 bytes (32 samples and 160 runs do); a larger
  * microbatch's table is first copied to the device on `stream` from one of
  * the pool's pinned staging buffers.
  * Errors: EINVAL (also more than 1024 samples or images, or a microbatch of
@@ -393,7 +394,7 @@ fp_status pack_microbatch(fp_pool* p, const uint64_t* sample_ids, int32_t n,
  * graph capture, tight serving loops, harnesses that forbid allocation): the
  * same arguments, result and errors, but the call allocates nothing, host or
  * device, on success. A microbatch whose row table does not fit the kernel
- * arguments (more than 32 samples or 160 runs) has it copied, from one of the
+ * arguments (see pack_microbatch) has it copied, from one of the
  * staging buffers pool_create allocated, into a 64 KiB device scratch array
  * of the library, one per GPU, which holds the largest table a pack can have;
  * a larger table returns ECAPACITY (it cannot occur within the limits of

@@ -46,9 +46,12 @@ constexpr int kSmallChunkRowBytes = 10240;
 constexpr int kPackPerCU = 8;        // k_pack workgroups resident per CU (occupancy 8)
 constexpr int kTail1Vecs = 512;
 constexpr int kTail2Vecs = 256;
-constexpr int kInlineSamples = 32;   // sample lengths passed by value to k_pack
-constexpr int kInlineRuns = 160;     // runs passed by value to k_pack
-constexpr int kBuckets = 64;         // row buckets of the run index
+constexpr int kBuckets = 64;         // row buckets of the run index at most
+constexpr int kMinBuckets = 16;      // and at least, in a table passed by value that could not hold kBuckets
+// A pack of more samples or runs than these is not captured into a graph
+// (each such run table fits the kernel arguments with kBuckets buckets).
+constexpr int kCaptureSamples = 32;
+constexpr int kCaptureRuns = 160;
 constexpr int kWaveRows = 16;        // rows per wave resolved with scalar loads in k_pack
 constexpr int kMaxPackSamples = 1024;  // per microbatch (bounds the staged run table)
 constexpr int kMaxPackImages = 1024;
@@ -80,18 +83,22 @@ constexpr int32_t kTablePlainLoads = 4;
 constexpr int64_t kPlainTableMaxBytes = 5ll << 29;   // 2.5 GiB
 constexpr int64_t kMaxMetaBytes = 1ll << 33;
 
-// What the pack kernel reads, passed by value. The run table (sample
-// lengths, runs, bucket index) follows the scalar fields; kernel arguments
-// are captured at launch, so a microbatch of up to kInlineSamples samples and
-// kInlineRuns runs needs no staging copy. A larger one is copied to device
-// memory first, laid out at the given byte offsets. For each row bucket b,
-// brun[b] is a copy of the run holding row b << bucket_shift and bucket[b]
-// that run's index, so a row of the same run is resolved with one load, and a
-// later row steps on from there. The table capacities are template
-// parameters: PackArgs is the general form, PackArgsSmall a compact one for
-// microbatches of a few samples, whose smaller kernel arguments take less
-// host time to launch.
-template <int kSamples, int kRuns, int kBucketCount>
+// The run table: the samples' lengths, their runs, and the bucket index: for
+// each row bucket b a copy of the run holding row b << shift, then that run's
+// index (16 bits), so a row of the same run is resolved with one load, and a
+// later row steps on from there. Byte offsets of the parts; size 0: no table.
+struct RunTable {
+  int32_t runs, bucket_runs, bucket_index, size;
+  int32_t n_buckets, shift;   // buckets hold 2^shift rows
+};
+
+// What the pack kernel reads, passed by value. The run table follows the
+// scalar fields; kernel arguments are captured at launch, so a microbatch
+// whose table fits needs no copy of it. A larger one is copied to device
+// memory first. The table's room is a template parameter: PackArgs is the
+// general form, PackArgsSmall a compact one for microbatches of a few
+// samples, whose smaller kernel arguments take less host time to launch.
+template <int kBytes>
 struct PackArgsT {
   const uint8_t* meta;        // device metadata arena
   const uint64_t* pte;        // device page table, index = (gva - gva_start) / page_bytes
@@ -113,25 +120,21 @@ struct PackArgsT {
   uint64_t pb_mul;            // d / page_bytes == umulhi64(d, pb_mul) >> pb_shift for d < 2^52
   int32_t pt_shift;
   int32_t pb_shift;
-  alignas(16) int32_t lens[kSamples];   // sample lengths (rows), in pack order
-  alignas(16) PackRun runs[kRuns];
-  alignas(16) PackRun brun[kBucketCount];
-  uint16_t bucket[kBucketCount];
-  static constexpr int kMaxSamples = kSamples, kMaxRuns = kRuns, kMaxBuckets = kBucketCount;
+  alignas(16) uint8_t run_table[kBytes];
+  static constexpr int kTableBytes = kBytes;
 };
-using PackArgs = PackArgsT<kInlineSamples, kInlineRuns, kBuckets>;
-using PackArgsSmall = PackArgsT<8, 24, 16>;
+using PackArgs = PackArgsT<3840>;
+using PackArgsSmall = PackArgsT<704>;
 // The pack's kernel arguments, 64 bytes of leading scalars (preloaded into
 // registers) and this struct, stay within 4 KiB.
 static_assert(sizeof(PackArgs) + 64 <= 4096, "kernel arguments stay within 4 KiB");
-static_assert(offsetof(PackArgs, lens) == offsetof(PackArgsSmall, lens), "same scalar fields");
+static_assert(offsetof(PackArgs, run_table) == offsetof(PackArgsSmall, run_table), "same scalar fields");
 
 // A pack launch: the kernel's arguments and, host side, its geometry.
 struct PackPlan {
   PackArgs a;
-  const uint8_t* staged;      // staged run table, or null = the arrays in `a`
+  const uint8_t* staged;      // staged run table, or null = the one in `a`
   bool small;                 // launch with PackArgsSmall (its table copied from `a`)
-  int32_t n_runs, n_buckets;  // entries of the table in `a`
   int32_t max_chunk_rows;     // rows one chunk can touch
   int32_t g0, g1;             // workgroups [0, g0): full chunks; [g0, g1): kTail1Vecs; then kTail2Vecs
   int32_t t1, t2;             // first vectors of the two tail stages (t1 = g0 * full chunk)
@@ -197,7 +200,8 @@ size_t pack_lds_bytes(const PackPlan& pl);
 Divisors make_divisors(int64_t row_bytes, int64_t page_tokens, uint64_t page_bytes);
 // Chunk geometry of a pack (g0, g1, t1, t2) for a device with n_cu compute units.
 void pack_chunks(PackPlan* pl, int n_cu);
-hipError_t launch_pack(const PackPlan& pl, hipStream_t stream);
+// Launches a pack; `done`, if not null, completes with its kernel.
+hipError_t launch_pack(const PackPlan& pl, hipStream_t stream, hipEvent_t done);
 // Launches a write; `done` completes with its kernel.
 hipError_t launch_write(const WritePlan& pl, int n_cu, hipStream_t stream, hipEvent_t done);
 // Measurement aids with the pack's geometry: a plain copy of `vecs` 16-byte

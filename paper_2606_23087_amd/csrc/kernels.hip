@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kPackBlock) void k_pack(int32_t g0, int32_t g1, int
   const RunIndex cx{h.bucket_shift, h.off_brun, h.off_bucket};
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const uint8_t* tb = h.tb ? h.tb : reinterpret_cast<const uint8_t*>(a.lens);
+  const uint8_t* tb = h.tb ? h.tb : a.run_table;
   int my_skip = 0;                                  // a row of this chunk is not copied
   int my_table = 0;                                 // a row of this chunk is an embedding-table row
 
@@ -518,39 +518,34 @@ void pack_chunks(PackPlan* pl, int n_cu) {
   chunk_geometry((int64_t)pl->a.n_tokens * (pl->a.row_bytes >> 4), n_cu, pl);
 }
 
-// The compact arguments of a small pack: the same scalar fields, the table
-// copied into the smaller arrays, offsets relative to them.
-static void small_args(const PackPlan& pl, PackArgsSmall* s) {
-  std::memcpy(static_cast<void*>(s), &pl.a, offsetof(PackArgs, lens));
-  std::memcpy(s->lens, pl.a.lens, sizeof(int32_t) * (size_t)pl.a.n);
-  std::memcpy(s->runs, pl.a.runs, sizeof(PackRun) * (size_t)pl.n_runs);
-  std::memcpy(s->brun, pl.a.brun, sizeof(PackRun) * (size_t)pl.n_buckets);
-  std::memcpy(s->bucket, pl.a.bucket, sizeof(uint16_t) * (size_t)pl.n_buckets);
-  s->off_runs = (int32_t)(offsetof(PackArgsSmall, runs) - offsetof(PackArgsSmall, lens));
-  s->off_brun = (int32_t)(offsetof(PackArgsSmall, brun) - offsetof(PackArgsSmall, lens));
-  s->off_bucket = (int32_t)(offsetof(PackArgsSmall, bucket) - offsetof(PackArgsSmall, lens));
-}
-
+// An event recorded after a kernel costs the stream about 3 us; a launch's own
+// stop event next to nothing.
 template <int VPT, class Args>
-static void launch_pack_as(const PackPlan& pl, const Args& a, int grid, int32_t total, hipStream_t stream) {
-  hipLaunchKernelGGL((k_pack<VPT, Args>), dim3(grid), dim3(kPackBlock), pack_lds_bytes(pl), stream, pl.g0, pl.g1,
-                     pl.t1, pl.t2, pl.div_mul, pl.div_shift, a.bucket_shift, pl.staged, a.off_brun, a.off_bucket,
-                     total, a);
+static void launch_pack_as(const PackPlan& pl, const Args& a, int grid, int32_t total, hipStream_t stream,
+                           hipEvent_t done) {
+  if (done)
+    hipExtLaunchKernelGGL((k_pack<VPT, Args>), dim3(grid), dim3(kPackBlock), pack_lds_bytes(pl), stream, nullptr, done,
+                          0, pl.g0, pl.g1, pl.t1, pl.t2, pl.div_mul, pl.div_shift, a.bucket_shift, pl.staged,
+                          a.off_brun, a.off_bucket, total, a);
+  else
+    hipLaunchKernelGGL((k_pack<VPT, Args>), dim3(grid), dim3(kPackBlock), pack_lds_bytes(pl), stream, pl.g0, pl.g1,
+                       pl.t1, pl.t2, pl.div_mul, pl.div_shift, a.bucket_shift, pl.staged, a.off_brun, a.off_bucket,
+                       total, a);
 }
 
-hipError_t launch_pack(const PackPlan& pl, hipStream_t stream) {
+hipError_t launch_pack(const PackPlan& pl, hipStream_t stream, hipEvent_t done) {
   const int64_t vecs = (int64_t)pl.a.n_tokens * (pl.a.row_bytes >> 4);
   const int64_t grid64 = pl.g1 + (vecs - pl.t2 + kTail2Vecs - 1) / kTail2Vecs;
   const int grid = grid64 > 0 ? (int)grid64 : 1;
   const int32_t total = (int32_t)vecs;               // the host keeps this below 2^31
   if (pl.small) {
-    PackArgsSmall s{};
-    small_args(pl, &s);
-    if (pl.vpt == 2) launch_pack_as<2>(pl, s, grid, total, stream);
-    else launch_pack_as<kVecsPerThread>(pl, s, grid, total, stream);
+    PackArgsSmall s;
+    std::memcpy(static_cast<void*>(&s), &pl.a, sizeof(s));
+    if (pl.vpt == 2) launch_pack_as<2>(pl, s, grid, total, stream, done);
+    else launch_pack_as<kVecsPerThread>(pl, s, grid, total, stream, done);
   } else {
-    if (pl.vpt == 2) launch_pack_as<2>(pl, pl.a, grid, total, stream);
-    else launch_pack_as<kVecsPerThread>(pl, pl.a, grid, total, stream);
+    if (pl.vpt == 2) launch_pack_as<2>(pl, pl.a, grid, total, stream, done);
+    else launch_pack_as<kVecsPerThread>(pl, pl.a, grid, total, stream, done);
   }
   return hipGetLastError();
 }

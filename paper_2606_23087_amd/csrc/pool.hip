@@ -291,8 +291,7 @@ struct fp_pool {
   // allocates no host memory. Used under `mu`.
   std::vector<SampleRec*> pk_recs;
   std::vector<int32_t> pk_lens;
-  std::vector<fp::PackRun> pk_runs, pk_brun;
-  std::vector<uint16_t> pk_bucket;
+  std::vector<fp::PackRun> pk_runs;
 
   uint64_t page_gva(int tier, int64_t idx) const { return seg_start[tier] + (uint64_t)idx * (uint64_t)pb; }
   int page_index(uint64_t gva, int64_t* idx) const {
@@ -782,8 +781,6 @@ fp_status pool_create(const fp_pool_config* cfg_in, fp_pool** out) {
     p->pk_recs.resize(fp::kMaxPackSamples);
     p->pk_lens.resize(fp::kMaxPackSamples);
     p->pk_runs.resize(kMaxPackRuns);
-    p->pk_brun.resize(fp::kBuckets);
-    p->pk_bucket.resize(fp::kBuckets);
     p->meta.init(c.meta_bytes);
     p->free_slots.resize((size_t)c.max_samples);
     for (int64_t i = 0; i < c.max_samples; ++i) p->free_slots[(size_t)i] = (int32_t)(c.max_samples - 1 - i);
@@ -1438,22 +1435,47 @@ static int32_t image_word(const fp_pool* p, const SampleRec& r) {
   return (int32_t)(r.page_off / 8);
 }
 
-// Bucket index of runs covering rows [0, total) (run k starts where run k-1
-// ends): at most max_buckets buckets of 2^shift rows; bucket b gets the run
-// holding its first row and that run's number. Returns the bucket count.
-static int32_t build_buckets(const fp::PackRun* runs, int32_t n_runs, int64_t total, int32_t max_buckets,
-                             int32_t* shift_out, fp::PackRun* brun, uint16_t* bucket) {
+// Bucket shift that covers rows [0, total) with at most max_buckets buckets
+// of 2^shift rows, and the bucket count.
+static int32_t bucket_shift(int64_t total, int32_t max_buckets, int32_t* n_buckets) {
   int32_t shift = 0;
   while (total > 0 && ((total - 1) >> shift) >= max_buckets) ++shift;
-  const int32_t nb = total > 0 ? (int32_t)(((total - 1) >> shift) + 1) : 0;
-  for (int32_t b = 0, k = 0; b < nb; ++b) {
-    const int64_t first = (int64_t)b << shift;
+  *n_buckets = total > 0 ? (int32_t)(((total - 1) >> shift) + 1) : 0;
+  return shift;
+}
+
+// Layout of a run table of n samples and n_runs runs over `total` rows with
+// as many buckets, up to max_buckets, as fit `room` bytes; size 0 when not
+// even kMinBuckets do.
+static fp::RunTable table_layout(int32_t n, int32_t n_runs, int64_t total, size_t room, int32_t max_buckets) {
+  fp::RunTable t{};
+  t.runs = (4 * n + 15) & ~15;
+  t.bucket_runs = t.runs + (int32_t)sizeof(fp::PackRun) * n_runs;
+  // A bucket takes a run and a 16-bit index; the kernel reads the indices in
+  // pairs, so their number is rounded up to even.
+  const int64_t fit = ((int64_t)room - t.bucket_runs) / (2 * ((int64_t)sizeof(fp::PackRun) + 2)) * 2;
+  if (fit < std::min(max_buckets, fp::kMinBuckets)) return t;
+  t.shift = bucket_shift(total, (int32_t)std::min<int64_t>(fit, max_buckets), &t.n_buckets);
+  t.bucket_index = t.bucket_runs + (int32_t)sizeof(fp::PackRun) * t.n_buckets;
+  t.size = std::max(t.bucket_index + 2 * (t.n_buckets + (t.n_buckets & 1)), 16);
+  return t;
+}
+
+// Writes the run table of runs covering rows [0, total) (run k starts where
+// run k-1 ends) at `dst`.
+static void fill_table(const fp::RunTable& t, const int32_t* lens, int32_t n, const fp::PackRun* runs, int32_t n_runs,
+                       uint8_t* dst) {
+  if (n) std::memcpy(dst, lens, 4 * (size_t)n);
+  if (n_runs) std::memcpy(dst + t.runs, runs, sizeof(fp::PackRun) * (size_t)n_runs);
+  fp::PackRun* brun = reinterpret_cast<fp::PackRun*>(dst + t.bucket_runs);
+  uint16_t* index = reinterpret_cast<uint16_t*>(dst + t.bucket_index);
+  for (int32_t b = 0, k = 0; b < t.n_buckets; ++b) {
+    const int64_t first = (int64_t)b << t.shift;
     while (k + 1 < n_runs && runs[k].end <= first) ++k;
-    bucket[b] = (uint16_t)k;
+    index[b] = (uint16_t)k;
     brun[b] = runs[k];
   }
-  *shift_out = shift;
-  return nb;
+  if (t.n_buckets & 1) index[t.n_buckets] = 0;
 }
 
 // pack_microbatch, and (scratch_dev != null) its variant that stages a large
@@ -1568,29 +1590,33 @@ static fp_status pack_impl(fp_pool* p, const uint64_t* sample_ids, int32_t n, co
     }
     if (n_runs) runs[n_runs - 1].end = row;
   }
-  // A microbatch of a few samples and runs launches with the compact kernel
-  // arguments (less host time per launch), whose bucket index is shorter.
-  const bool small = n <= fp::PackArgsSmall::kMaxSamples && n_runs <= fp::PackArgsSmall::kMaxRuns;
-  int32_t shift = 0;
-  const int32_t n_buckets = build_buckets(runs, n_runs, total, small ? fp::PackArgsSmall::kMaxBuckets : fp::kBuckets,
-                                          &shift, p->pk_brun.data(), p->pk_bucket.data());
-  const int32_t bucket_len = n_buckets + (n_buckets & 1);
-  a.bucket_shift = shift;
+  // The run table travels in the kernel arguments when it fits: in the compact
+  // ones (less host time per launch) with at most 16 buckets, else in the
+  // general ones with 64 buckets or, for many samples or runs, as few as 16.
+  // A larger table is copied to the device first, which takes the stream a
+  // copy and its gap, about 2.3 us a pack of 90 short samples; searching
+  // 32 buckets instead of 64 costs less.
+  fp::RunTable t = table_layout(n, n_runs, total, fp::PackArgsSmall::kTableBytes, fp::kMinBuckets);
+  const bool small = t.size > 0;
+  if (!small) t = table_layout(n, n_runs, total, fp::PackArgs::kTableBytes, fp::kBuckets);
+  const bool staged = t.size == 0;
+  if (staged) t = table_layout(n, n_runs, total, kScratchBytes, fp::kBuckets);
+  a.bucket_shift = t.shift;
+  a.off_runs = t.runs;
+  a.off_brun = t.bucket_runs;
+  a.off_bucket = t.bucket_index;
 
   pl.max_chunk_rows = (int32_t)std::min<int64_t>(total, fp::kChunkVecs / vpr + 2);
   pl.small = small;
-  pl.n_runs = n_runs;
-  pl.n_buckets = n_buckets;
   fp::pack_chunks(&pl, p->n_cu);
 
-  const bool staged = n > fp::kInlineSamples || n_runs > fp::kInlineRuns;
   const bool captured = capturing(hs);
   if (captured) {
     // A captured pack is one kernel whose arguments hold the whole
     // microbatch, so a replay packs the same samples again.
-    if (staged)
+    if (n > fp::kCaptureSamples || n_runs > fp::kCaptureRuns)
       return fail(FP_ESTATE, "a pack of more than %d samples or %d runs cannot be captured into a graph",
-                  fp::kInlineSamples, fp::kInlineRuns);
+                  fp::kCaptureSamples, fp::kCaptureRuns);
     // No event queries during capture: the writes must already be known complete.
     for (int32_t i = 0; i < n; ++i)
       if (recs[i]->written >= 0)
@@ -1599,52 +1625,33 @@ static fp_status pack_impl(fp_pool* p, const uint64_t* sample_ids, int32_t n, co
   }
   Stage* s = nullptr;
   if (!staged) {
-    if (n) std::memcpy(a.lens, lens, 4 * (size_t)n);
-    if (n_runs) std::memcpy(a.runs, runs, sizeof(fp::PackRun) * (size_t)n_runs);
-    if (n_buckets) std::memcpy(a.bucket, p->pk_bucket.data(), 2 * (size_t)n_buckets);
-    if (n_buckets) std::memcpy(a.brun, p->pk_brun.data(), sizeof(fp::PackRun) * (size_t)n_buckets);
-    a.off_runs = (int32_t)(offsetof(fp::PackArgs, runs) - offsetof(fp::PackArgs, lens));
-    a.off_brun = (int32_t)(offsetof(fp::PackArgs, brun) - offsetof(fp::PackArgs, lens));
-    a.off_bucket = (int32_t)(offsetof(fp::PackArgs, bucket) - offsetof(fp::PackArgs, lens));
+    fill_table(t, lens, n, runs, n_runs, a.run_table);
     pl.staged = nullptr;
   } else {
-    const size_t o_runs = ((size_t)4 * n + 15) & ~(size_t)15;
-    const size_t o_br = o_runs + sizeof(fp::PackRun) * (size_t)n_runs;
-    const size_t o_b = o_br + sizeof(fp::PackRun) * (size_t)n_buckets;
-    const size_t bytes = o_b + 2 * (size_t)bucket_len;
     uint8_t* dest = nullptr;
     if (noalloc) {
-      if (bytes > scratch_bytes)
-        return fail(FP_ECAPACITY, "run table of %zu bytes exceeds the %zu-byte scratch", bytes, scratch_bytes);
-      fp_status st = stage_acquire(p, bytes, 0, &s);        // never allocates: buffers hold kStageHostMin
+      if ((size_t)t.size > scratch_bytes)
+        return fail(FP_ECAPACITY, "run table of %d bytes exceeds the %zu-byte scratch", t.size, scratch_bytes);
+      fp_status st = stage_acquire(p, (size_t)t.size, 0, &s);   // never allocates: buffers hold kStageHostMin
       if (st != FP_OK) return st;
       dest = scratch_dev;
     } else {
-      fp_status st = stage_acquire(p, bytes, bytes, &s);
+      fp_status st = stage_acquire(p, (size_t)t.size, (size_t)t.size, &s);
       if (st != FP_OK) return st;
       dest = s->dev;
     }
-    std::memset(s->host, 0, bytes);
-    if (n) std::memcpy(s->host, lens, 4 * (size_t)n);
-    if (n_runs) std::memcpy(s->host + o_runs, runs, sizeof(fp::PackRun) * (size_t)n_runs);
-    if (n_buckets) std::memcpy(s->host + o_br, p->pk_brun.data(), sizeof(fp::PackRun) * (size_t)n_buckets);
-    if (n_buckets) std::memcpy(s->host + o_b, p->pk_bucket.data(), 2 * (size_t)n_buckets);
-    FP_HIP(hipMemcpyAsync(dest, s->host, bytes, hipMemcpyHostToDevice, hs));
+    std::memset(s->host, 0, (size_t)t.size);
+    fill_table(t, lens, n, runs, n_runs, s->host);
+    FP_HIP(hipMemcpyAsync(dest, s->host, (size_t)t.size, hipMemcpyHostToDevice, hs));
     pl.staged = dest;
-    a.off_runs = (int32_t)o_runs;
-    a.off_brun = (int32_t)o_br;
-    a.off_bucket = (int32_t)o_b;
   }
   {
     fp_status st = order_after_writes(p, recs, (size_t)n, hs);
     if (st != FP_OK) return st;
   }
-  hipError_t e = fp::launch_pack(pl, hs);
+  hipError_t e = fp::launch_pack(pl, hs, s ? s->ev : nullptr);
   if (e != hipSuccess) return fail(FP_EHIP, "pack kernel: %s", hipGetErrorString(e));
-  if (s) {
-    fp_status st = stage_release(s, hs);
-    if (st != FP_OK) return st;
-  }
+  if (s) s->pending = true;
   // Remember the stream as a reader of each sample; a free records its event
   // there (no event per pack: events between back-to-back packs slow them).
   for (int32_t i = 0; i < n; ++i) {
