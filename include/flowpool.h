@@ -215,13 +215,13 @@ fp_status pool_free_sample(fp_pool* p, uint64_t sample_id);
 fp_status pool_reclaim(fp_pool* p, int32_t wait, int64_t* out_deferred_pages);
 
 /* Tier migration (Sec. 3.2: the pool spans HBM and host DRAM; data moves
- * between tiers by the copy engine the pair of tiers calls for). Moves every
+ * between tiers by the means the pair of tiers calls for). Moves every
  * page of the samples sample_ids[0..n) that is not in `tier` (FP_TIER_HBM or
  * FP_TIER_HOST) into a free page of `tier`: pages in visual-row order, each
  * taking the next page of the tier's free stack, so a sample's GVAs change
- * and its bytes do not. The copies are asynchronous DMA copies on `stream`
- * (host <-> device through the SDMA engines; device <-> device as a copy),
- * followed by the upload of the samples' new page lists. Packs and plans
+ * and its bytes do not. One kernel on `stream`, of a few workgroups that
+ * read or write the host tier's memory across the link, copies the pages and
+ * uploads the samples' new page lists. Packs and plans
  * enqueued later on other streams wait for them; packs enqueued earlier keep
  * reading the old pages, which return to their tier's free stack
  * (last-page-first) once the copies and those packs have completed. Used to

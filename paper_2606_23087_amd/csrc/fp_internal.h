@@ -196,6 +196,35 @@ struct WritePlan {
   int32_t div_shift;
 };
 
+// A migration's work list, in pinned host memory: the pages to copy, then per
+// sample its new page list.
+struct alignas(16) MigratePage {
+  uint64_t src, dst;          // device-visible addresses
+  int64_t vecs;               // 16-byte vectors to copy (the last page of a sample may be partial)
+  int64_t pad;
+};
+struct alignas(16) MigrateList {
+  int64_t words_at;           // byte offset of the list in the work list's buffer
+  int64_t meta_off;           // where it goes in the arena; also the descriptor's new page_off
+  int32_t n_words;
+  int32_t slot;
+  int64_t pad;
+};
+// Workgroups that copy pages, by the target tier, and vectors of a page one of
+// them moves per step (see k_migrate).
+constexpr int kMigrateGrid[2] = {10, 16};
+constexpr int kMigrateVecs = kPackBlock * 4;
+
+struct MigrateArgs {
+  const uint8_t* stage;       // n_pages MigratePage, n_lists MigrateList, the lists' words
+  uint8_t* meta;
+  SampleDesc* desc_table;
+  int64_t n_pages;
+  int64_t steps_per_page;     // kMigrateVecs each, of a whole page
+  int32_t n_lists;
+  int32_t tier;               // target
+};
+
 size_t pack_lds_bytes(const PackPlan& pl);
 Divisors make_divisors(int64_t row_bytes, int64_t page_tokens, uint64_t page_bytes);
 // Chunk geometry of a pack (g0, g1, t1, t2) for a device with n_cu compute units.
@@ -204,6 +233,8 @@ void pack_chunks(PackPlan* pl, int n_cu);
 hipError_t launch_pack(const PackPlan& pl, hipStream_t stream, hipEvent_t done);
 // Launches a write; `done` completes with its kernel.
 hipError_t launch_write(const WritePlan& pl, int n_cu, hipStream_t stream, hipEvent_t done);
+// Launches a migration; `done` completes with its kernel.
+hipError_t launch_migrate(const MigrateArgs& a, hipStream_t stream, hipEvent_t done);
 // Measurement aids with the pack's geometry: a plain copy of `vecs` 16-byte
 // vectors (chunks sized as for rows of row_bytes), and a gather of n_rows
 // rows of row_bytes from the device addresses rows_src[] into consecutive

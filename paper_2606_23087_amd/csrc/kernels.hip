@@ -10,6 +10,8 @@
 // k_write : the producer's write of one sample's image rows into its pages,
 //           through the same page table (Sec. 3.2, producer side), the upload
 //           of its metadata and publication of its descriptor.
+// k_migrate: the copy of a migration's pages between the tiers and the upload
+//           of the samples' new page lists (Sec. 3.2).
 // k_cost  : per-sample cost K*l + l^2 for the planner (Sec. 3.4).
 //
 // Nothing here is a dense contraction, so there is no MFMA: the pack is a
@@ -485,6 +487,74 @@ __global__ __launch_bounds__(kPackBlock) void k_write(int32_t g0, int32_t g1, in
   else write_chunk<VPT, false>(a, vis, div_mul, div_shift, v0, v1, s_dst, tid);
 }
 
+// One step of a migration: n vectors of a page (at most kMigrateVecs). kWhole
+// as in write_chunk.
+template <bool kWhole>
+__device__ __forceinline__ void migrate_step(const uint8_t* src, uint8_t* dst, int n, int tid) {
+  constexpr int N = kMigrateVecs / kPackBlock;
+  u32x4 v[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int e = u * kPackBlock + tid;
+    v[u] = load16(src + (size_t)(kWhole ? e : min(e, n - 1)) * 16);
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int e = u * kPackBlock + tid;
+    if (kWhole || e < n) store16(dst + (size_t)e * 16, v[u]);
+  }
+}
+
+// Tier migration (Sec. 3.2): workgroups [0, n_lists) each put one sample's new
+// page list into the arena and its place into the descriptor; a few others
+// walk the pages in steps of kMigrateVecs vectors, reading or writing the host
+// tier's memory directly.
+//
+// The link to the host bounds it, and all it needs of the chip is enough bytes
+// in flight to cover the link's latency. 97 MB to the host tier take 1.69 ms
+// (57 GB/s, the rate of one large copy) with 16 workgroups of 16 KiB each. The
+// other way 16 read as fast, but a read across the link holds up the loads of
+// the packs that share its CU: beside a stream of packs of 35.4 us each, the
+// packs take 37.9, 39.3, 41.5 and 48 us with 8, 12, 16 and 24 workgroups and
+// the migration 2.65, 2.27, 2.07 and 1.9 ms. As copies by the DMA engines,
+// one per run of adjacent pages, both directions took 2.7 ms and the packs
+// beside them 37.3 us.
+__global__ __launch_bounds__(kPackBlock) void k_migrate(MigrateArgs a) {
+  const int tid = threadIdx.x;
+  const uint8_t* pages = a.stage;
+  if ((int)blockIdx.x < a.n_lists) {
+    const uint8_t* l = a.stage + sizeof(MigratePage) * (size_t)a.n_pages + sizeof(MigrateList) * (size_t)blockIdx.x;
+    const int64_t words_at = ld<true, int64_t>(l + offsetof(MigrateList, words_at));
+    const int64_t meta_off = ld<true, int64_t>(l + offsetof(MigrateList, meta_off));
+    const int32_t n_words = ld<true, int32_t>(l + offsetof(MigrateList, n_words));
+    const int32_t slot = ld<true, int32_t>(l + offsetof(MigrateList, slot));
+    uint64_t* to = reinterpret_cast<uint64_t*>(a.meta + meta_off);
+    for (int i = tid; i < n_words; i += kPackBlock) to[i] = ld<false, uint64_t>(a.stage + words_at + 8 * (int64_t)i);
+    if (tid == 0) a.desc_table[slot].page_off = meta_off;
+    return;
+  }
+  const int64_t first = (int64_t)blockIdx.x - a.n_lists;
+  const int64_t grid = (int64_t)gridDim.x - a.n_lists;
+  const int64_t page_stride = grid / a.steps_per_page, step_stride = grid % a.steps_per_page;
+  int64_t page = first / a.steps_per_page, step = first % a.steps_per_page;
+  while (page < a.n_pages) {
+    const uint8_t* e = pages + sizeof(MigratePage) * (size_t)page;
+    const uint64_t src = ld<true, uint64_t>(e + offsetof(MigratePage, src));
+    const uint64_t dst = ld<true, uint64_t>(e + offsetof(MigratePage, dst));
+    const int64_t left = ld<true, int64_t>(e + offsetof(MigratePage, vecs)) - step * kMigrateVecs;
+    const uint8_t* from = reinterpret_cast<const uint8_t*>(src) + step * kMigrateVecs * 16;
+    uint8_t* to = reinterpret_cast<uint8_t*>(dst) + step * kMigrateVecs * 16;
+    if (left >= kMigrateVecs) migrate_step<true>(from, to, kMigrateVecs, tid);
+    else if (left > 0) migrate_step<false>(from, to, (int)left, tid);
+    page += page_stride;
+    step += step_stride;
+    if (step >= a.steps_per_page) {
+      step -= a.steps_per_page;
+      ++page;
+    }
+  }
+}
+
 __global__ __launch_bounds__(kBlock) void k_cost(const SampleDesc* __restrict__ desc,
                                                   const int32_t* __restrict__ slots, int32_t n,
                                                   int64_t k, int64_t* __restrict__ out) {
@@ -687,6 +757,13 @@ hipError_t launch_write(const WritePlan& w, int n_cu, hipStream_t stream, hipEve
     if (geo.vpt == 2) launch_write_as<2>(w, s, geo, total, n_meta, stream, done);
     else launch_write_as<kVecsPerThread>(w, s, geo, total, n_meta, stream, done);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_migrate(const MigrateArgs& a, hipStream_t stream, hipEvent_t done) {
+  const int64_t steps = a.n_pages * a.steps_per_page;
+  const int grid = a.n_lists + (int)std::min<int64_t>(steps, kMigrateGrid[a.tier]);
+  hipExtLaunchKernelGGL(k_migrate, dim3(grid), dim3(kPackBlock), 0, stream, nullptr, done, 0, a);
   return hipGetLastError();
 }
 

@@ -1101,34 +1101,26 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
       unreserve();
       return st;
     }
-    // Staging: the new page lists, then each sample's new page_off for its descriptor.
-    size_t stage_bytes = 0;
-    for (SampleRec* r : recs) stage_bytes += (size_t)align16(8 * (int64_t)r->pages.size()) + 16;
+    // Staging: the work list of the migration kernel (pages, then the samples'
+    // new page lists).
+    size_t at = sizeof(fp::MigratePage) * (size_t)need + sizeof(fp::MigrateList) * recs.size();
+    size_t stage_bytes = at;
+    for (SampleRec* r : recs) stage_bytes += (size_t)align16(8 * (int64_t)r->pages.size());
     Stage* sg = nullptr;
     st = stage_acquire(p, stage_bytes, 0, &sg);
+    int32_t ev = -1;
+    if (st == FP_OK && p->events.acquire(&ev) != hipSuccess) st = fail(FP_EHIP, "migration event");
     if (st != FP_OK) {
       unreserve();
       return st;
     }
-    // From here on nothing fails half-way but a HIP error: take the pages.
+    // From here on nothing fails half-way but the launch: take the pages.
     std::vector<std::vector<uint64_t>> new_pages(recs.size());
     std::vector<std::vector<uint64_t>> old_pages(recs.size());
-    // Consecutive pages whose old and new frames are both adjacent inside one
-    // backing chunk are copied as one run.
-    struct Run { uint64_t src, dst, bytes; int src_chunk, dst_chunk; };
-    std::vector<Run> runs;
     const int64_t P = p->cfg.page_tokens;
-    auto chunk_of = [&](uint64_t addr) {
-      int id = 0;
-      for (int t = 0; t < 2; ++t) {
-        const uint64_t chunk_span = (uint64_t)p->frames_per_chunk[t] * (uint64_t)p->pb;
-        for (void* c : p->chunks[t]) {
-          if (addr >= (uint64_t)c && addr < (uint64_t)c + chunk_span) return id;
-          ++id;
-        }
-      }
-      return -1;
-    };
+    auto frame = [&](uint64_t gva) { return p->pte[(size_t)page_number(p, gva)] & fp::PTE_ADDR_MASK; };
+    fp::MigratePage* entry = reinterpret_cast<fp::MigratePage*>(sg->host);
+    fp::MigrateList* list = reinterpret_cast<fp::MigrateList*>(sg->host + sizeof(fp::MigratePage) * (size_t)need);
     for (size_t j = 0; j < recs.size(); ++j) {
       SampleRec& r = *recs[j];
       new_pages[j] = r.pages;
@@ -1138,52 +1130,36 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
         p->used[tier][i] = 1;
         p->n_free[tier] -= 1;
         const uint64_t gva = p->page_gva(tier, i);
-        const uint64_t src = p->pte[(size_t)((r.pages[(size_t)k] - p->gva_start) / (uint64_t)p->pb)] & fp::PTE_ADDR_MASK;
-        const uint64_t dst = p->pte[(size_t)((gva - p->gva_start) / (uint64_t)p->pb)] & fp::PTE_ADDR_MASK;
         const int64_t rows = std::min<int64_t>(P, r.n_vis - (int64_t)k * P);
-        const uint64_t bytes = (uint64_t)(rows * p->rb);
-        const int sc = chunk_of(src), dc = chunk_of(dst);
-        if (!runs.empty() && runs.back().src + runs.back().bytes == src && runs.back().dst + runs.back().bytes == dst &&
-            runs.back().bytes % (uint64_t)p->pb == 0 && runs.back().src_chunk == sc && runs.back().dst_chunk == dc)
-          runs.back().bytes += bytes;
-        else
-          runs.push_back(Run{src, dst, bytes, sc, dc});
+        *entry++ = fp::MigratePage{frame(r.pages[(size_t)k]), frame(gva), rows * (p->rb / 16), 0};
         old_pages[j].push_back(r.pages[(size_t)k]);
         new_pages[j][(size_t)k] = gva;
       }
+      *list++ = fp::MigrateList{(int64_t)at, pl_off[j], (int32_t)new_pages[j].size(), r.slot, 0};
+      std::memcpy(sg->host + at, new_pages[j].data(), 8 * new_pages[j].size());
+      at += (size_t)align16(8 * (int64_t)new_pages[j].size());
     }
-    hipError_t e = hipSuccess;
-    for (const Run& run : runs) {
-      e = hipMemcpyAsync((void*)run.dst, (const void*)run.src, run.bytes, hipMemcpyDefault, hs);
-      if (e != hipSuccess) break;
-    }
-    size_t at = 0;
-    for (size_t j = 0; e == hipSuccess && j < recs.size(); ++j) {
-      const size_t nb = 8 * new_pages[j].size();
-      std::memcpy(sg->host + at, new_pages[j].data(), nb);
-      e = hipMemcpyAsync(p->meta_dev + pl_off[j], sg->host + at, nb, hipMemcpyHostToDevice, hs);
-      at += (size_t)align16((int64_t)nb);
-      if (e != hipSuccess) break;
-      std::memcpy(sg->host + at, &pl_off[j], 8);
-      e = hipMemcpyAsync(&p->desc_dev[recs[j]->slot].page_off, sg->host + at, 8, hipMemcpyHostToDevice, hs);
-      at += 16;
-    }
-    int32_t ev = -1;
-    if (e == hipSuccess) e = p->events.acquire(&ev);
-    if (e == hipSuccess) e = hipEventRecord(p->events.ev[(size_t)ev], hs);
+    fp::MigrateArgs ma{};
+    ma.stage = sg->host_dev;
+    ma.meta = p->meta_dev;
+    ma.desc_table = p->desc_dev;
+    ma.n_pages = need;
+    ma.steps_per_page = (p->pb / 16 + fp::kMigrateVecs - 1) / fp::kMigrateVecs;
+    ma.n_lists = (int32_t)recs.size();
+    ma.tier = tier;
+    const hipError_t e = fp::launch_migrate(ma, hs, p->events.ev[(size_t)ev]);
     if (e != hipSuccess) {
-      // Queued copies may still run: wait for them, then put everything back.
-      (void)hipStreamSynchronize(hs);
-      if (ev >= 0) p->events.unref(ev);
+      p->events.unref(ev);
       for (size_t j = 0; j < recs.size(); ++j) {
         std::vector<uint64_t> taken;
         for (int32_t k : moving[j]) taken.push_back(new_pages[j][(size_t)k]);
         release_pages(p, taken);
       }
       unreserve();
-      return fail(FP_EHIP, "migration copies: %s", hipGetErrorString(e));
+      return fail(FP_EHIP, "migration kernel: %s", hipGetErrorString(e));
     }
-    st = stage_release(sg, hs);
+    p->events.ref(ev);
+    sg->shared = ev;
     // The pages left behind and the old page lists wait for the copies and for
     // every pack that may still read them.
     for (size_t j = 0; j < recs.size(); ++j) {
