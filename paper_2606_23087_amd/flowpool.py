@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 from typing import Optional
 
 import numpy as np
@@ -28,9 +29,9 @@ if not os.path.exists(LIB_PATH):
 # other way round, the process ends up with two HSA runtimes, and the second
 # one to start finds no device.
 try:
-    import torch  # noqa: F401
+    import torch
 except ImportError:
-    pass
+    torch = None
 
 _lib = C.CDLL(LIB_PATH)
 ABI_VERSION = 5   # FP_ABI_VERSION of include/flowpool.h that these bindings follow
@@ -122,12 +123,48 @@ def _check(status: int, where: str) -> None:
         raise FlowPoolError(status, where, _lib.fp_last_error().decode(errors="replace"))
 
 
+# The host time of a small call is mostly its marshalling, so what it uses is
+# picked by cost: a buffer view takes 0.1 us an array (numpy's ``ctypes``
+# attribute 1.2), an ``array`` of 80 ids 0.6 us (a ctypes array 5), the raw
+# handle of torch's current stream 0.2 us (its stream object 2.7). A pack of 4
+# samples takes 7.3 us of host time with them (11.4 without), a write of one
+# image 7.0 us (15.1); the C calls alone take 4.2 and 4.3 us.
+
+_EMPTY = {t: t._type_() for t in (_i32p, _i64p, _u64p, _u8p)}   # not null, as an empty array's data is
+
+
+def _at(a, ptype):
+    """ctypes argument for a parameter of type ``ptype``: the data of a numpy array or ``array``, kept alive by it."""
+    if len(a) == 0:
+        return _EMPTY[ptype]
+    try:
+        return ptype._type_.from_buffer(a)
+    except (TypeError, ValueError):      # read-only, or no element in spite of its length
+        return np.asarray(a).ctypes.data_as(ptype)
+
+
 def _arr(a, dtype, ptype):
-    """Contiguous numpy array of ``dtype`` and a ctypes pointer to it (None if a is None)."""
+    """Contiguous numpy array of ``dtype`` and a ctypes argument for its data (None if a is None)."""
     if a is None:
         return None, None
     a = np.ascontiguousarray(a, dtype=dtype)
-    return a, a.ctypes.data_as(ptype)
+    return a, _at(a, ptype)
+
+
+def _ids(ids):
+    """Sample ids as a contiguous array of uint64 and a ctypes argument for its data."""
+    if isinstance(ids, (list, tuple)):
+        try:
+            a = array("Q", ids)
+            return a, _at(a, _u64p)
+        except (TypeError, OverflowError):
+            pass
+    return _arr(ids, np.uint64, _u64p)
+
+
+def _rows(ntok) -> int:
+    """Sum of a sample's image row counts (numpy's own sum takes 0.8 us whatever the size)."""
+    return sum(ntok.tolist()) if ntok.ndim == 1 and len(ntok) <= 64 else int(ntok.sum(dtype=np.int64))
 
 
 def _ptr(x) -> Optional[int]:
@@ -156,19 +193,21 @@ def _buf(x, nbytes: int, name: str, device: Optional[int] = None) -> Optional[in
     if on a GPU, be on ``device`` (when given)."""
     if x is None or isinstance(x, int):
         return _ptr(x)
-    if device is not None and x.is_cuda and x.device.index != device:
+    if device is not None and x.is_cuda and x.get_device() != device:
         raise ValueError(f"{name} is on cuda:{x.device.index}, the pool on cuda:{device}")
     if not x.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if x.numel() * x.element_size() < nbytes:
-        raise ValueError(f"{name} holds {x.numel() * x.element_size()} bytes, the call needs {nbytes}")
+    if x.nbytes < nbytes:
+        raise ValueError(f"{name} holds {x.nbytes} bytes, the call needs {nbytes}")
     return _ptr(x)
 
 
 def _stream(s) -> Optional[int]:
     if s is None:
-        import torch
-        return int(torch.cuda.current_stream().cuda_stream)
+        if torch is not None and torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        from torch.cuda import current_stream
+        return int(current_stream().cuda_stream)
     if isinstance(s, int):
         return s
     return int(s.cuda_stream)
@@ -228,10 +267,10 @@ def pool_write_sample(pool: int, text_ids, img_pos, img_ntok, vis_emb=None, page
     w, wp = _arr(page_tier_wish, np.uint8, _u8p)
     sid = C.c_uint64()
     rb = 2 * _HIDDEN.get(pool, 0)
-    vis = _buf(vis_emb, int(v.sum(dtype=np.int64)) * rb if v is not None else 0, "vis_emb", _DEVICE.get(pool))
-    _check(_lib.pool_write_sample(pool, tp, len(t), pp, vp, len(p), vis, wp, _stream(stream),
-                                  C.byref(sid)), "pool_write_sample")
-    return int(sid.value)
+    vis = _buf(vis_emb, _rows(v) * rb if v is not None else 0, "vis_emb", _DEVICE.get(pool))
+    _check(_lib.pool_write_sample(pool, tp, len(t), pp, vp, len(p), vis, wp, _stream(stream), sid),
+           "pool_write_sample")
+    return sid.value
 
 
 def pool_free_sample(pool: int, sample_id: int) -> None:
@@ -248,7 +287,7 @@ def pool_reclaim(pool: int, wait: bool = False) -> int:
 
 def pool_release_captured(pool: int, sample_ids) -> None:
     """End a captured pack's hold on its samples (once its graph will not be replayed again)."""
-    ids, idp = _arr(sample_ids, np.uint64, _u64p)
+    ids, idp = _ids(sample_ids)
     _check(_lib.pool_release_captured(pool, idp, len(ids)), "pool_release_captured")
 
 
@@ -259,7 +298,7 @@ def pool_forget_stream(pool: int, stream) -> None:
 
 def pool_migrate(pool: int, sample_ids, tier: int, stream=None) -> int:
     """Move the samples' pages into ``tier`` (FP_TIER_HBM / FP_TIER_HOST). Returns pages moved."""
-    ids, idp = _arr(sample_ids, np.uint64, _u64p)
+    ids, idp = _ids(sample_ids)
     moved = C.c_int64()
     _check(_lib.pool_migrate(pool, idp, len(ids), tier, _stream(stream), C.byref(moved)), "pool_migrate")
     return int(moved.value)
@@ -268,7 +307,7 @@ def pool_migrate(pool: int, sample_ids, tier: int, stream=None) -> int:
 def plan_microbatches(pool: int, sample_ids, capacity: int, n_mb: int, cost_k: int, stream=None,
                       policy: int = FP_PLAN_LPT):
     """Returns dict(assign, mb_tokens, mb_cost_scaled, mb_max_len, sample_cost_scaled)."""
-    ids, idp = _arr(sample_ids, np.uint64, _u64p)
+    ids, idp = _ids(sample_ids)
     n = len(ids)
     assign = np.empty(n, np.int32)
     tok = np.empty(n_mb, np.int32)
@@ -276,9 +315,8 @@ def plan_microbatches(pool: int, sample_ids, capacity: int, n_mb: int, cost_k: i
     mx = np.empty(n_mb, np.int32)
     sc = np.empty(n, np.int64)
     _check(_lib.plan_microbatches(pool, idp, n, capacity, n_mb, cost_k, policy,
-                                  assign.ctypes.data_as(_i32p), tok.ctypes.data_as(_i32p),
-                                  cst.ctypes.data_as(_i64p), mx.ctypes.data_as(_i32p),
-                                  sc.ctypes.data_as(_i64p), _stream(stream)), "plan_microbatches")
+                                  _at(assign, _i32p), _at(tok, _i32p), _at(cst, _i64p), _at(mx, _i32p),
+                                  _at(sc, _i64p), _stream(stream)), "plan_microbatches")
     return dict(assign=assign, mb_tokens=tok, mb_cost_scaled=cst, mb_max_len=mx, sample_cost_scaled=sc)
 
 
@@ -350,7 +388,7 @@ def plan_dynamic_packing(lengths, capacity: int, n_ranks: int, n_buckets: int):
 
 def plan_pool_packing(pool: int, sample_ids, capacity: int, n_ranks: int, n_buckets: int):
     """Alg. 1 on resident samples (their pool lengths); same result as plan_dynamic_packing."""
-    ids, idp = _arr(sample_ids, np.uint64, _u64p)
+    ids, idp = _ids(sample_ids)
     return _packing_call(_lib.plan_pool_packing, "plan_pool_packing", (pool, idp), len(ids), capacity,
                          n_ranks, n_buckets)
 
@@ -360,7 +398,11 @@ def pack_microbatch(pool: int, sample_ids, embed_table, vocab: int, out_emb, out
                     stream=None, _entry=None):
     """Enqueue the pack of ``sample_ids`` into ``out_emb``. Returns (n_tokens, max_seqlen)."""
     if isinstance(sample_ids, (list, tuple)):
-        ids = idp = (C.c_uint64 * len(sample_ids))(*sample_ids)   # cheaper per call than a numpy round trip
+        try:
+            ids = array("Q", sample_ids)
+            idp = _at(ids, _u64p)
+        except (TypeError, OverflowError):       # ctypes takes any integers, modulo 2^64
+            ids = idp = (C.c_uint64 * len(sample_ids))(*sample_ids)
     else:
         ids, idp = _arr(sample_ids, np.uint64, _u64p)
     n_tok = C.c_int32()
@@ -372,9 +414,9 @@ def pack_microbatch(pool: int, sample_ids, embed_table, vocab: int, out_emb, out
     _check(entry(pool, idp, len(ids), _buf(embed_table, max(int(vocab), 0) * rb, "embed_table", dev),
                  vocab, _buf(out_emb, cap * rb, "out_emb", dev), out_rows_cap,
                  _buf(out_cu_seqlens, 4 * (len(ids) + 1), "out_cu_seqlens", dev),
-                 _buf(out_position_ids, 4 * cap, "out_position_ids", dev), C.byref(n_tok), C.byref(mx),
-                 tier_mask, _stream(stream)), entry.__name__)
-    return int(n_tok.value), int(mx.value)
+                 _buf(out_position_ids, 4 * cap, "out_position_ids", dev), n_tok, mx, tier_mask, _stream(stream)),
+           entry.__name__)
+    return n_tok.value, mx.value
 
 
 def pack_microbatch_noalloc(pool: int, sample_ids, embed_table, vocab: int, out_emb, out_rows_cap: int,
