@@ -225,6 +225,20 @@ struct MigrateArgs {
   int32_t tier;               // target
 };
 
+// The slots of a plan's samples travel in the cost kernel's arguments up to
+// this many (within 4 KiB with the other arguments), so that the kernel does
+// not read them across the link.
+constexpr int kCostSlots = 960;
+struct CostArgs {
+  const SampleDesc* desc;
+  const int32_t* slots;       // pinned host memory, or null = `slot`
+  int64_t* out;
+  int64_t k;
+  int32_t n;
+  int32_t slot[kCostSlots];
+};
+static_assert(sizeof(CostArgs) <= 4096, "kernel arguments stay within 4 KiB");
+
 size_t pack_lds_bytes(const PackPlan& pl);
 Divisors make_divisors(int64_t row_bytes, int64_t page_tokens, uint64_t page_bytes);
 // Chunk geometry of a pack (g0, g1, t1, t2) for a device with n_cu compute units.
@@ -242,7 +256,10 @@ hipError_t launch_migrate(const MigrateArgs& a, hipStream_t stream, hipEvent_t d
 hipError_t launch_copy(const void* src, void* dst, int64_t vecs, int64_t row_bytes, int n_cu, hipStream_t stream);
 hipError_t launch_gather(const uint64_t* rows_src, int32_t n_rows, int64_t row_bytes, void* dst, int n_cu,
                          hipStream_t stream);
-hipError_t launch_cost(const SampleDesc* desc, const int32_t* slots, int32_t n, int64_t k,
-                       int64_t* out_cost, hipStream_t stream);
+// Costs of the samples in slots[0, n) (host memory) into out_cost (device-visible). More than
+// kCostSlots of them are read through slots_dev, the GPU's view of the same array in pinned memory.
+// `done` completes with the kernel.
+hipError_t launch_cost(const SampleDesc* desc, const int32_t* slots, const int32_t* slots_dev, int32_t n, int64_t k,
+                       int64_t* out_cost, hipStream_t stream, hipEvent_t done);
 
 }  // namespace fp
