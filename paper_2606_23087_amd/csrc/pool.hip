@@ -451,18 +451,36 @@ void defer_or_release(fp_pool* p, Deferred&& d) {
   }
 }
 
+// What one call has found out about a reader stream: the event that follows
+// its work so far, or -1 if it needs none.
+struct StreamMark {
+  void* stream;
+  int32_t event;
+};
+
 // Appends to `events` (each with a reference of its own) what follows every
-// pack that has read sample r: an event recorded now on each reader stream
-// that still has work queued, and the events that stand in for retired reader
-// streams.
-fp_status mark_readers(fp_pool* p, const SampleRec& r, std::vector<int32_t>* events) {
+// pack that has read sample r: an event recorded on each reader stream that
+// still has work queued, and the events that stand in for retired reader
+// streams. A stream in `marks` is not asked or recorded again; the others are
+// added to it (an event in it is kept by the list it was first appended to).
+fp_status mark_readers(fp_pool* p, const SampleRec& r, std::vector<StreamMark>* marks, std::vector<int32_t>* events) {
   for (int32_t e : r.reader_events) {
     p->events.ref(e);
     events->push_back(e);
   }
   for (void* st : r.readers) {
+    auto known = std::find_if(marks->begin(), marks->end(), [&](const StreamMark& m) { return m.stream == st; });
+    if (known != marks->end()) {
+      if (known->event < 0) continue;
+      p->events.ref(known->event);
+      events->push_back(known->event);
+      continue;
+    }
     const hipError_t q = hipStreamQuery((hipStream_t)st);
-    if (q == hipSuccess) continue;
+    if (q == hipSuccess) {
+      marks->push_back({st, -1});
+      continue;
+    }
     if (q != hipErrorNotReady) return fail(FP_EHIP, "stream query: %s", hipGetErrorString(q));
     int32_t ev = -1;
     hipError_t e = p->events.acquire(&ev);
@@ -472,6 +490,7 @@ fp_status mark_readers(fp_pool* p, const SampleRec& r, std::vector<int32_t>* eve
       return fail(FP_EHIP, "reader event: %s", hipGetErrorString(e));
     }
     events->push_back(ev);
+    marks->push_back({st, ev});
   }
   return FP_OK;
 }
@@ -991,7 +1010,8 @@ fp_status pool_free_sample(fp_pool* p, uint64_t sample_id) {
     Deferred d;
     // An event recorded now on every stream that packed the sample and still
     // has work queued follows those packs; idle streams need none.
-    fp_status st = mark_readers(p, r, &d.events);
+    std::vector<StreamMark> marks;
+    fp_status st = mark_readers(p, r, &marks, &d.events);
     if (st != FP_OK) {
       for (int32_t x : d.events) p->events.unref(x);
       return st;
@@ -1155,7 +1175,10 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
     p->events.ref(ev);
     sg->shared = ev;
     // The pages left behind and the old page lists wait for the copies and for
-    // every pack that may still read them.
+    // every pack that may still read them. On the migration's own stream the
+    // copies follow those packs; any other reader stream gets one event for all
+    // samples, where an event per sample took the stream 4.6 us each.
+    std::vector<StreamMark> marks{{stream, -1}};
     for (size_t j = 0; j < recs.size(); ++j) {
       SampleRec& r = *recs[j];
       Deferred d;
@@ -1172,7 +1195,7 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
       r.pl_len = pl_bytes;
       r.page_off = pl_off[j];
       r.pages = std::move(new_pages[j]);
-      fp_status ms = mark_readers(p, r, &d.events);
+      fp_status ms = mark_readers(p, r, &marks, &d.events);
       if (ms != FP_OK) {
         // Without an event on every reader, wait for the whole device instead.
         (void)hipDeviceSynchronize();
