@@ -177,9 +177,11 @@ struct WriteArgsT {
   uint32_t page[kCapacity];   // page numbers (WriteArgsSmall: of page 0)
   static constexpr int kPages = kCapacity;
 };
-// Kernel arguments cost host time by their size (a launch measured 2.5 us
-// with 64 bytes of them, 3.5 with 512, 4.7 with 1024), so writes whose page
-// numbers need no list take the small form.
+// A list costs host time to fill and to pass: the C call of a write takes 3.93
+// us with 4 scattered pages and 3.87 with 4 consecutive ones, 5.01 and 4.69
+// with 180. So writes whose page numbers need no list take the small form; a
+// list longer than this is read from the staging buffer (4.86 and 4.73 us with
+// 250 pages), by a kernel long enough to hide the reads across the link.
 constexpr int kInlinePages = 192;
 using WriteArgs = WriteArgsT<kInlinePages>;
 using WriteArgsSmall = WriteArgsT<1>;
