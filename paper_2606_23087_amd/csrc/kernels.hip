@@ -19,8 +19,6 @@
 
 #include "fp_internal.h"
 
-#include <hip/hip_ext.h>
-
 #include <algorithm>
 #include <cstring>
 
@@ -566,6 +564,26 @@ __global__ __launch_bounds__(kBlock) void k_cost(CostArgs a) {
   }
 }
 
+template <class T>
+struct As {
+  using type = T;
+};
+
+// Launches a kernel of kPackBlock or kBlock threads a workgroup; `done`, if
+// not null, completes with it. The status is the launch's own: the thread's
+// last error (hipGetLastError) may be an earlier call's, of this library or of
+// the caller, and the kernel is queued all the same.
+// An event recorded after a kernel costs the stream about 3 us; a launch's own
+// stop event next to nothing.
+template <class... P>
+static hipError_t launch(void (*kernel)(P...), int grid, int block, size_t lds, hipStream_t stream, hipEvent_t done,
+                         const typename As<P>::type&... arg) {
+  void* args[] = {const_cast<void*>(static_cast<const void*>(&arg))...};
+  const void* f = reinterpret_cast<const void*>(kernel);
+  if (done) return hipExtLaunchKernel(f, dim3(grid), dim3(block), args, lds, stream, nullptr, done, 0);
+  return hipLaunchKernel(f, dim3(grid), dim3(block), args, lds, stream);
+}
+
 size_t pack_lds_bytes(const PackPlan& pl) { return sizeof(uint64_t) * (size_t)std::max(pl.max_chunk_rows, 1); }
 
 // Chunk geometry over `vecs` vectors: full chunks of kPackBlock * vpt
@@ -589,19 +607,11 @@ void pack_chunks(PackPlan* pl, int n_cu) {
   chunk_geometry((int64_t)pl->a.n_tokens * (pl->a.row_bytes >> 4), n_cu, pl);
 }
 
-// An event recorded after a kernel costs the stream about 3 us; a launch's own
-// stop event next to nothing.
 template <int VPT, class Args>
-static void launch_pack_as(const PackPlan& pl, const Args& a, int grid, int32_t total, hipStream_t stream,
-                           hipEvent_t done) {
-  if (done)
-    hipExtLaunchKernelGGL((k_pack<VPT, Args>), dim3(grid), dim3(kPackBlock), pack_lds_bytes(pl), stream, nullptr, done,
-                          0, pl.g0, pl.g1, pl.t1, pl.t2, pl.div_mul, pl.div_shift, a.bucket_shift, pl.staged,
-                          a.off_brun, a.off_bucket, total, a);
-  else
-    hipLaunchKernelGGL((k_pack<VPT, Args>), dim3(grid), dim3(kPackBlock), pack_lds_bytes(pl), stream, pl.g0, pl.g1,
-                       pl.t1, pl.t2, pl.div_mul, pl.div_shift, a.bucket_shift, pl.staged, a.off_brun, a.off_bucket,
-                       total, a);
+static hipError_t launch_pack_as(const PackPlan& pl, const Args& a, int grid, int32_t total, hipStream_t stream,
+                                 hipEvent_t done) {
+  return launch(&k_pack<VPT, Args>, grid, kPackBlock, pack_lds_bytes(pl), stream, done, pl.g0, pl.g1, pl.t1, pl.t2,
+                pl.div_mul, pl.div_shift, a.bucket_shift, pl.staged, a.off_brun, a.off_bucket, total, a);
 }
 
 hipError_t launch_pack(const PackPlan& pl, hipStream_t stream, hipEvent_t done) {
@@ -612,13 +622,11 @@ hipError_t launch_pack(const PackPlan& pl, hipStream_t stream, hipEvent_t done) 
   if (pl.small) {
     PackArgsSmall s;
     std::memcpy(static_cast<void*>(&s), &pl.a, sizeof(s));
-    if (pl.vpt == 2) launch_pack_as<2>(pl, s, grid, total, stream, done);
-    else launch_pack_as<kVecsPerThread>(pl, s, grid, total, stream, done);
-  } else {
-    if (pl.vpt == 2) launch_pack_as<2>(pl, pl.a, grid, total, stream, done);
-    else launch_pack_as<kVecsPerThread>(pl, pl.a, grid, total, stream, done);
+    return pl.vpt == 2 ? launch_pack_as<2>(pl, s, grid, total, stream, done)
+                       : launch_pack_as<kVecsPerThread>(pl, s, grid, total, stream, done);
   }
-  return hipGetLastError();
+  return pl.vpt == 2 ? launch_pack_as<2>(pl, pl.a, grid, total, stream, done)
+                     : launch_pack_as<kVecsPerThread>(pl, pl.a, grid, total, stream, done);
 }
 
 // ---------------------------------------------------------------------------
@@ -707,13 +715,8 @@ hipError_t launch_copy(const void* src, void* dst, int64_t vecs, int64_t row_byt
   PackPlan pl{};
   plain_geometry(vecs, row_bytes, n_cu, &pl);
   const int grid = (int)(pl.g1 + (vecs - pl.t2 + kTail2Vecs - 1) / kTail2Vecs);
-  if (pl.vpt == 2)
-    hipLaunchKernelGGL(k_copy<2>, dim3(grid), dim3(kPackBlock), 0, stream, pl.g0, pl.g1, pl.t1, pl.t2, (int32_t)vecs,
-                       (const uint8_t*)src, (uint8_t*)dst);
-  else
-    hipLaunchKernelGGL(k_copy<kVecsPerThread>, dim3(grid), dim3(kPackBlock), 0, stream, pl.g0, pl.g1, pl.t1, pl.t2,
-                       (int32_t)vecs, (const uint8_t*)src, (uint8_t*)dst);
-  return hipGetLastError();
+  return launch(pl.vpt == 2 ? &k_copy<2> : &k_copy<kVecsPerThread>, grid, kPackBlock, 0, stream, nullptr, pl.g0, pl.g1,
+                pl.t1, pl.t2, (int32_t)vecs, (const uint8_t*)src, (uint8_t*)dst);
 }
 
 hipError_t launch_gather(const uint64_t* rows_src, int32_t n_rows, int64_t row_bytes, void* dst, int n_cu,
@@ -725,22 +728,18 @@ hipError_t launch_gather(const uint64_t* rows_src, int32_t n_rows, int64_t row_b
   const Divisors dv = make_divisors(row_bytes, 1, 16);
   const int grid = (int)(pl.g1 + (vecs - pl.t2 + kTail2Vecs - 1) / kTail2Vecs);
   const size_t lds = sizeof(uint64_t) * (size_t)std::min<int64_t>(n_rows, kChunkVecs / (row_bytes >> 4) + 2);
-  if (pl.vpt == 2)
-    hipLaunchKernelGGL(k_gather<2>, dim3(grid), dim3(kPackBlock), lds, stream, pl.g0, pl.g1, pl.t1, pl.t2,
-                       (int32_t)vecs, dv.div_mul, dv.div_shift, (int32_t)row_bytes, rows_src, (uint8_t*)dst);
-  else
-    hipLaunchKernelGGL(k_gather<kVecsPerThread>, dim3(grid), dim3(kPackBlock), lds, stream, pl.g0, pl.g1, pl.t1,
-                       pl.t2, (int32_t)vecs, dv.div_mul, dv.div_shift, (int32_t)row_bytes, rows_src, (uint8_t*)dst);
-  return hipGetLastError();
+  return launch(pl.vpt == 2 ? &k_gather<2> : &k_gather<kVecsPerThread>, grid, kPackBlock, lds, stream, nullptr, pl.g0,
+                pl.g1, pl.t1, pl.t2, (int32_t)vecs, dv.div_mul, dv.div_shift, (int32_t)row_bytes, rows_src,
+                (uint8_t*)dst);
 }
 
 template <int VPT, class Args>
-static void launch_write_as(const WritePlan& w, const Args& a, const PackPlan& geo, int32_t total, int32_t n_meta,
-                            hipStream_t stream, hipEvent_t done) {
+static hipError_t launch_write_as(const WritePlan& w, const Args& a, const PackPlan& geo, int32_t total,
+                                  int32_t n_meta, hipStream_t stream, hipEvent_t done) {
   const int grid = n_meta + (total > 0 ? geo.g1 + (total - geo.t2 + kTail2Vecs - 1) / kTail2Vecs : 0);
   const size_t lds = sizeof(uint64_t) * (size_t)std::max(w.max_chunk_rows, 1);
-  hipExtLaunchKernelGGL((k_write<VPT, Args>), dim3(grid), dim3(kPackBlock), lds, stream, nullptr, done, 0, geo.g0,
-                        geo.g1, geo.t1, geo.t2, w.div_mul, w.vis, w.div_shift, total, n_meta, a);
+  return launch(&k_write<VPT, Args>, grid, kPackBlock, lds, stream, done, geo.g0, geo.g1, geo.t1, geo.t2, w.div_mul,
+                w.vis, w.div_shift, total, n_meta, a);
 }
 
 hipError_t launch_write(const WritePlan& w, int n_cu, hipStream_t stream, hipEvent_t done) {
@@ -749,23 +748,19 @@ hipError_t launch_write(const WritePlan& w, int n_cu, hipStream_t stream, hipEve
   const int32_t n_meta = std::max((a.meta_vecs + kMetaVecs - 1) / kMetaVecs, 1);
   PackPlan geo{};
   plain_geometry(total, a.row_bytes, n_cu, &geo);
-  if (w.inline_pages) {
-    if (geo.vpt == 2) launch_write_as<2>(w, a, geo, total, n_meta, stream, done);
-    else launch_write_as<kVecsPerThread>(w, a, geo, total, n_meta, stream, done);
-  } else {
-    WriteArgsSmall s;
-    std::memcpy(static_cast<void*>(&s), &a, sizeof(s));
-    if (geo.vpt == 2) launch_write_as<2>(w, s, geo, total, n_meta, stream, done);
-    else launch_write_as<kVecsPerThread>(w, s, geo, total, n_meta, stream, done);
-  }
-  return hipGetLastError();
+  if (w.inline_pages)
+    return geo.vpt == 2 ? launch_write_as<2>(w, a, geo, total, n_meta, stream, done)
+                        : launch_write_as<kVecsPerThread>(w, a, geo, total, n_meta, stream, done);
+  WriteArgsSmall s;
+  std::memcpy(static_cast<void*>(&s), &a, sizeof(s));
+  return geo.vpt == 2 ? launch_write_as<2>(w, s, geo, total, n_meta, stream, done)
+                      : launch_write_as<kVecsPerThread>(w, s, geo, total, n_meta, stream, done);
 }
 
 hipError_t launch_migrate(const MigrateArgs& a, hipStream_t stream, hipEvent_t done) {
   const int64_t steps = a.n_pages * a.steps_per_page;
   const int grid = a.n_lists + (int)std::min<int64_t>(steps, kMigrateGrid[a.tier]);
-  hipExtLaunchKernelGGL(k_migrate, dim3(grid), dim3(kPackBlock), 0, stream, nullptr, done, 0, a);
-  return hipGetLastError();
+  return launch(&k_migrate, grid, kPackBlock, 0, stream, done, a);
 }
 
 Divisors make_divisors(int64_t row_bytes, int64_t page_tokens, uint64_t page_bytes) {
@@ -799,8 +794,7 @@ hipError_t launch_cost(const SampleDesc* desc, const int32_t* slots, const int32
   a.k = k;
   a.n = n;
   std::memcpy(a.slot, slots, sizeof(int32_t) * (size_t)std::min<int32_t>(n, kCostSlots));
-  hipExtLaunchKernelGGL(k_cost, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, stream, nullptr, done, 0, a);
-  return hipGetLastError();
+  return launch(&k_cost, (n + kBlock - 1) / kBlock, kBlock, 0, stream, done, a);
 }
 
 }  // namespace fp

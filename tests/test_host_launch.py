@@ -1,0 +1,81 @@
+"""What the library makes of a launch's status, on a stand-in HIP runtime (CPU
+only; see host_runtime.py).
+
+An error that an earlier call of the thread left behind (of this library or of
+the caller's own code) is not a launch's: writes, migrations, plans, packs and
+the measurement aids enqueued with one pending succeed, keep their pages and
+leave the error for whoever asks for it.
+"""
+
+import ctypes as C
+
+import pytest
+
+import host_runtime as hr
+from host_runtime import Pool
+
+S1, S2 = 0x51, 0x52        # stream handles; the stand-in never looks into one
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return hr.build(tmp_path_factory.mktemp("host"))
+
+
+@pytest.fixture()
+def pool(lib):
+    lib.stub_pending(0)
+    lib.stub_launch(0)
+    lib.stub_record(0)
+    lib.stub_busy(0)
+    lib.stub_capturing(0)
+    p = Pool(lib)
+    p.log()
+    yield p
+    for f in (lib.stub_launch, lib.stub_record, lib.stub_busy, lib.stub_capturing):
+        f(0)
+    p.destroy()
+
+
+MANY = 100                 # samples of a pack whose run table is copied to the device
+
+
+def _call(pool, what, samples):
+    """One call of a kind on stream S1, over resident samples."""
+    if what == "write":
+        return pool.write(3, 10, S1)[0]
+    if what == "migrate":
+        return pool.migrate(samples[:2], 1, S1)
+    if what == "plan":
+        return pool.plan(samples[:3], S1)
+    if what == "copy":
+        return pool.lib.fp_copy_bytes(C.c_void_p(1 << 20), C.c_void_p(1 << 21), 4096, 64, S1)
+    if what == "gather":
+        return pool.lib.fp_gather_rows(C.c_void_p(1 << 20), 8, 64, C.c_void_p(1 << 21), S1)
+    ids = (samples * MANY)[:MANY] if "staged" in what else samples[:2]
+    return pool.pack(ids, S1, "noalloc" in what)
+
+
+CALLS = ["write", "migrate", "plan", "pack", "pack staged", "pack noalloc", "pack staged noalloc", "copy", "gather"]
+KERNEL = dict(write="k_write", migrate="k_migrate", plan="k_cost", copy="k_copy", gather="k_gather")
+
+
+@pytest.mark.parametrize("what", CALLS)
+def test_an_earlier_error_is_not_the_launch_s(pool, what):
+    samples = [pool.write(3, 10, S1)[1] for _ in range(4)]
+    assert pool.lib.pool_reclaim(pool.p, 1, None) == 0
+    hbm, host, n = pool.stats()
+    pool.log()
+    pool.lib.stub_pending(hr.INVALID_VALUE)
+    assert _call(pool, what, samples) == 0, pool.lib.fp_last_error()
+    assert pool.lib.stub_peek() == hr.INVALID_VALUE
+    launches = [l for l in pool.log() if l.startswith("launch")]
+    assert len(launches) == 1 and KERNEL.get(what, "k_pack") in launches[0]
+    if what == "write":
+        assert pool.stats() == (hbm - 3, host, n + 1)
+    elif what == "migrate":
+        # two samples' pages taken in the host tier; those they leave wait for the copies
+        pool.lib.pool_reclaim(pool.p, 1, None)
+        assert pool.stats() == (hbm + 6, host - 6, n)
+    else:
+        assert pool.stats() == (hbm, host, n)
