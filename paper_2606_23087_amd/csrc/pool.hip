@@ -539,6 +539,14 @@ bool capturing(hipStream_t stream) {
   return cs != hipStreamCaptureStatusNone;
 }
 
+// For a call that fails after it enqueued work, or may have (a launch can
+// report a failure with its kernel queued): waits for the stream, so that the
+// pages, staging buffer and event that work uses can be used again.
+fp_status fail_behind(hipStream_t stream, fp_status st) {
+  (void)hipStreamSynchronize(stream);
+  return st;
+}
+
 // A caller-provided tier backing: 256-byte aligned, at least `bytes` long
 // inside one allocation, and of the tier's kind: device memory of `device`
 // (HBM tier), or pinned host memory mapped into the GPU at the same address
@@ -955,8 +963,9 @@ fp_status pool_write_sample(fp_pool* p, const int32_t* text_ids, int32_t n_text,
     if (e != hipSuccess) return rollback(fail(FP_EHIP, "write event: %s", hipGetErrorString(e)));
     e = fp::launch_write(w, p->n_cu, hs, p->events.ev[(size_t)ev]);
     if (e != hipSuccess) {
+      st = fail_behind(hs, fail(FP_EHIP, "write kernel: %s", hipGetErrorString(e)));
       p->events.unref(ev);
-      return rollback(fail(FP_EHIP, "write kernel: %s", hipGetErrorString(e)));
+      return rollback(st);
     }
     if (s) {
       p->events.ref(ev);
@@ -1163,6 +1172,7 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
     ma.tier = tier;
     const hipError_t e = fp::launch_migrate(ma, hs, p->events.ev[(size_t)ev]);
     if (e != hipSuccess) {
+      st = fail_behind(hs, fail(FP_EHIP, "migration kernel: %s", hipGetErrorString(e)));
       p->events.unref(ev);
       for (size_t j = 0; j < recs.size(); ++j) {
         std::vector<uint64_t> taken;
@@ -1170,7 +1180,7 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
         release_pages(p, taken);
       }
       unreserve();
-      return fail(FP_EHIP, "migration kernel: %s", hipGetErrorString(e));
+      return st;
     }
     p->events.ref(ev);
     sg->shared = ev;
@@ -1289,8 +1299,9 @@ fp_status plan_microbatches(fp_pool* p, const uint64_t* sample_ids, int32_t n, i
       std::memcpy(s->host, slots.data(), 4 * (size_t)n);
       st = order_after_writes(p, recs.data(), recs.size(), hs);   // the descriptors come from the writes
       if (st != FP_OK) return st;
-      FP_HIP(fp::launch_cost(p->desc_dev, (const int32_t*)s->host, (const int32_t*)s->host_dev, n, cost_k,
-                             (int64_t*)(s->host_dev + slot_bytes), hs, s->ev));
+      const hipError_t e = fp::launch_cost(p->desc_dev, (const int32_t*)s->host, (const int32_t*)s->host_dev, n, cost_k,
+                                           (int64_t*)(s->host_dev + slot_bytes), hs, s->ev);
+      if (e != hipSuccess) return fail_behind(hs, fail(FP_EHIP, "cost kernel: %s", hipGetErrorString(e)));
       s->pending = true;
       st = distinct(n);
       FP_HIP(hipEventSynchronize(s->ev));
@@ -1655,15 +1666,17 @@ static fp_status pack_impl(fp_pool* p, const uint64_t* sample_ids, int32_t n, co
     }
     std::memset(s->host, 0, (size_t)t.size);
     fill_table(t, lens, n, runs, n_runs, s->host);
-    FP_HIP(hipMemcpyAsync(dest, s->host, (size_t)t.size, hipMemcpyHostToDevice, hs));
+    const hipError_t ce = hipMemcpyAsync(dest, s->host, (size_t)t.size, hipMemcpyHostToDevice, hs);
+    if (ce != hipSuccess) return fail_behind(hs, fail(FP_EHIP, "run table copy: %s", hipGetErrorString(ce)));
     pl.staged = dest;
   }
-  {
-    fp_status st = order_after_writes(p, recs, (size_t)n, hs);
-    if (st != FP_OK) return st;
+  const fp_status os = order_after_writes(p, recs, (size_t)n, hs);
+  if (os != FP_OK) return s ? fail_behind(hs, os) : os;
+  const hipError_t e = fp::launch_pack(pl, hs, s ? s->ev : nullptr);
+  if (e != hipSuccess) {
+    const fp_status st = fail(FP_EHIP, "pack kernel: %s", hipGetErrorString(e));
+    return captured ? st : fail_behind(hs, st);
   }
-  hipError_t e = fp::launch_pack(pl, hs, s ? s->ev : nullptr);
-  if (e != hipSuccess) return fail(FP_EHIP, "pack kernel: %s", hipGetErrorString(e));
   if (s) s->pending = true;
   // Remember the stream as a reader of each sample; a free records its event
   // there (no event per pack: events between back-to-back packs slow them).

@@ -17,6 +17,7 @@ std::string g_log;
 hipError_t g_pending = hipSuccess;    // what hipGetLastError would return
 hipError_t g_launch = hipSuccess;     // status of the next launches
 hipError_t g_record = hipSuccess;     // status of the next event records
+hipError_t g_wait = hipSuccess;       // status of the next stream waits
 bool g_busy = false;                  // streams and events have not finished
 bool g_capturing = false;
 int g_events = 0;
@@ -67,6 +68,7 @@ void stub_pending(int e) { g_pending = (hipError_t)e; }
 int stub_peek() { return (int)g_pending; }
 void stub_launch(int e) { g_launch = (hipError_t)e; }
 void stub_record(int e) { g_record = (hipError_t)e; }
+void stub_wait(int e) { g_wait = (hipError_t)e; }
 void stub_busy(int b) { g_busy = b != 0; }
 void stub_capturing(int c) { g_capturing = c != 0; }
 
@@ -137,7 +139,7 @@ hipError_t hipEventRecord(hipEvent_t, hipStream_t s) { note("record", s); return
 hipError_t hipEventSynchronize(hipEvent_t e) { note("event_sync", e); return hipSuccess; }
 hipError_t hipStreamQuery(hipStream_t) { return g_busy ? hipErrorNotReady : hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { note("stream_sync", s); return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) { note("stream_wait", s); return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) { note("stream_wait", s); return done(g_wait); }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
   *c = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;

@@ -24,15 +24,13 @@ def lib(tmp_path_factory):
 
 @pytest.fixture()
 def pool(lib):
-    lib.stub_pending(0)
-    lib.stub_launch(0)
-    lib.stub_record(0)
-    lib.stub_busy(0)
-    lib.stub_capturing(0)
+    settings = (lib.stub_pending, lib.stub_launch, lib.stub_record, lib.stub_wait, lib.stub_busy, lib.stub_capturing)
+    for f in settings:
+        f(0)
     p = Pool(lib)
     p.log()
     yield p
-    for f in (lib.stub_launch, lib.stub_record, lib.stub_busy, lib.stub_capturing):
+    for f in settings:
         f(0)
     p.destroy()
 
@@ -79,3 +77,48 @@ def test_an_earlier_error_is_not_the_launch_s(pool, what):
         assert pool.stats() == (hbm + 6, host - 6, n)
     else:
         assert pool.stats() == (hbm, host, n)
+
+
+@pytest.mark.parametrize("what", [c for c in CALLS if c not in ("copy", "gather")])
+def test_a_failed_launch_waits_before_it_gives_back(pool, what):
+    """A launch that reports a failure may still have queued its kernel, and a
+    staged pack has queued the copy of its table: the call waits for the stream
+    before what they use (pages, arena, staging buffer, event) can be used again."""
+    samples = [pool.write(3, 10, S1)[1] for _ in range(4)]
+    assert pool.lib.pool_reclaim(pool.p, 1, None) == 0
+    before, pages = pool.stats(), [pool.pages(i) for i in samples]
+    pool.log()
+    pool.lib.stub_launch(hr.LAUNCH_FAILURE)
+    assert _call(pool, what, samples) == -6          # EHIP
+    pool.lib.stub_launch(0)
+    log = pool.log()
+    at = next(i for i, l in enumerate(log) if l.startswith("launch"))
+    assert f"stream_sync {S1}" in log[at:], log
+    assert pool.stats() == before and [pool.pages(i) for i in samples] == pages
+    assert _call(pool, what, samples) == 0
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_a_pack_that_fails_behind_its_table_s_copy_waits_for_it(pool, noalloc):
+    samples = [pool.write(3, 10, S2)[1] for _ in range(4)]
+    pool.lib.stub_busy(1)                            # the writes, on another stream, have not finished
+    pool.lib.stub_wait(hr.INVALID_VALUE)
+    pool.log()
+    assert pool.pack((samples * MANY)[:MANY], S1, noalloc) == -6
+    pool.lib.stub_wait(0)
+    log = pool.log()
+    assert f"copy {S1}" in log and f"stream_sync {S1}" in log[log.index(f"copy {S1}"):], log
+
+
+def test_a_failed_launch_under_capture_does_not_wait(pool):
+    samples = [pool.write(3, 10, S1)[1] for _ in range(2)]
+    assert pool.lib.pool_reclaim(pool.p, 1, None) == 0
+    pool.log()
+    pool.lib.stub_capturing(1)
+    pool.lib.stub_launch(hr.LAUNCH_FAILURE)
+    assert pool.pack(samples, S1) == -6
+    assert not any("sync" in l for l in pool.log())  # a wait would end the capture
+    pool.lib.stub_launch(0)
+    assert pool.pack(samples, S1) == 0
+    assert pool.lib.pool_release_captured(pool.p, pool.ids(samples), 2) == 0
+    pool.lib.stub_capturing(0)
