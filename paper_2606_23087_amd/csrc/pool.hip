@@ -35,6 +35,9 @@ namespace {
 
 thread_local std::string t_err;
 
+// Sets the calling thread's message and returns `code`. A HIP error is taken
+// out of the runtime with that: left as the thread's last error, it would be
+// found, and taken for a failure of its own, by whoever asks next.
 fp_status fail(fp_status code, const char* fmt, ...) {
   char buf[512];
   va_list ap;
@@ -42,6 +45,7 @@ fp_status fail(fp_status code, const char* fmt, ...) {
   vsnprintf(buf, sizeof(buf), fmt, ap);
   va_end(ap);
   t_err = buf;
+  if (code == FP_EHIP) (void)hipGetLastError();
   return code;
 }
 
@@ -543,7 +547,7 @@ bool capturing(hipStream_t stream) {
 // report a failure with its kernel queued): waits for the stream, so that the
 // pages, staging buffer and event that work uses can be used again.
 fp_status fail_behind(hipStream_t stream, fp_status st) {
-  (void)hipStreamSynchronize(stream);
+  if (hipStreamSynchronize(stream) != hipSuccess) (void)hipGetLastError();
   return st;
 }
 

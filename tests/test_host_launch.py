@@ -12,6 +12,7 @@ import ctypes as C
 import pytest
 
 import host_runtime as hr
+from paper_2606_23087_amd import flowpool as fp
 from host_runtime import Pool
 
 S1, S2 = 0x51, 0x52        # stream handles; the stand-in never looks into one
@@ -122,3 +123,25 @@ def test_a_failed_launch_under_capture_does_not_wait(pool):
     assert pool.pack(samples, S1) == 0
     assert pool.lib.pool_release_captured(pool.p, pool.ids(samples), 2) == 0
     pool.lib.stub_capturing(0)
+
+
+def test_a_reported_hip_error_is_not_left_behind(pool):
+    """A call that has returned EHIP has reported its error; the thread's next
+    look at its last error (torch's after each of its launches, say) finds none."""
+    lib = pool.lib
+    cfg = fp.fp_pool_config()
+    lib.fp_config_init(C.byref(cfg))
+    cfg.hidden, cfg.page_tokens, cfg.hbm_pages, cfg.chunk_bytes = 1 << 20, 1 << 10, 1 << 19, 1 << 60
+    out = C.c_void_p()
+    assert lib.pool_create(C.byref(cfg), C.byref(out)) == -6 and not out.value      # 2^50 bytes
+    assert lib.stub_peek() == 0
+    i = pool.write(3, 10, S1)[1]
+    lib.stub_busy(1)
+    assert pool.pack([i], S2) == 0
+    lib.stub_record(hr.INVALID_VALUE)
+    assert lib.pool_free_sample(pool.p, i) == -6     # cannot record the reader's event
+    assert lib.stub_peek() == 0
+    lib.stub_launch(hr.LAUNCH_FAILURE)
+    for what in CALLS:
+        assert _call(pool, what, [i] * 4 if what not in ("migrate", "plan") else [i]) == -6
+        assert lib.stub_peek() == 0, what
