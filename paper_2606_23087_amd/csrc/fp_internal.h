@@ -198,13 +198,8 @@ struct WritePlan {
   int32_t div_shift;
 };
 
-// A migration's work list, in pinned host memory: the pages to copy, then per
-// sample its new page list.
-struct alignas(16) MigratePage {
-  uint64_t src, dst;          // device-visible addresses
-  int64_t vecs;               // 16-byte vectors to copy (the last page of a sample may be partial)
-  int64_t pad;
-};
+// A migration's work list, in pinned host memory: per sample its new page
+// list, then the pieces to copy.
 struct alignas(16) MigrateList {
   int64_t words_at;           // byte offset of the list in the work list's buffer
   int64_t meta_off;           // where it goes in the arena; also the descriptor's new page_off
@@ -212,17 +207,29 @@ struct alignas(16) MigrateList {
   int32_t slot;
   int64_t pad;
 };
-// Workgroups that copy pages, by the target tier, and vectors of a page one of
-// them moves per step (see k_migrate).
+struct alignas(16) MigratePiece {
+  uint64_t src, dst;          // device-visible addresses
+  uint32_t vecs;              // 16-byte vectors to copy, at most kMigratePieceVecs
+  uint32_t pad;
+  uint64_t pad1;
+};
+// Workgroups that copy pieces, by the target tier, and vectors of a piece a
+// wave moves per step (see k_migrate).
 constexpr int kMigrateGrid[2] = {10, 16};
-constexpr int kMigrateVecs = kPackBlock * 4;
+constexpr uint32_t kMigrateVecs = 64 * 4;
+constexpr int64_t kMigratePieceVecs = 1 << 30;
+// A page of at least this many steps is a piece of its own, of which at most
+// the last step moves less than a whole one. Smaller pages that are adjacent in
+// both tiers are taken together and cut into pieces of one step.
+constexpr int kMigratePageSteps = 8;
 
 struct MigrateArgs {
-  const uint8_t* stage;       // n_pages MigratePage, n_lists MigrateList, the lists' words
+  const uint8_t* stage;       // n_lists MigrateList, the lists' words, n_pieces MigratePiece
   uint8_t* meta;
   SampleDesc* desc_table;
-  int64_t n_pages;
-  int64_t steps_per_page;     // kMigrateVecs each, of a whole page
+  int64_t pieces_at;          // byte offset of the pieces
+  uint32_t n_pieces;
+  uint32_t steps_per_piece;   // kMigrateVecs each, of the longest piece
   int32_t n_lists;
   int32_t tier;               // target
 };

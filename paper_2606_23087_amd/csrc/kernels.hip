@@ -485,43 +485,54 @@ __global__ __launch_bounds__(kPackBlock) void k_write(int32_t g0, int32_t g1, in
   else write_chunk<VPT, false>(a, vis, div_mul, div_shift, v0, v1, s_dst, tid);
 }
 
-// One step of a migration: n vectors of a page (at most kMigrateVecs). kWhole
-// as in write_chunk.
+// One step of a migration, by one wave: n vectors of a piece (at most
+// kMigrateVecs). kWhole as in write_chunk.
 template <bool kWhole>
-__device__ __forceinline__ void migrate_step(const uint8_t* src, uint8_t* dst, int n, int tid) {
-  constexpr int N = kMigrateVecs / kPackBlock;
+__device__ __forceinline__ void migrate_step(const uint8_t* src, uint8_t* dst, uint32_t n, uint32_t lane) {
+  constexpr int N = kMigrateVecs / 64;
   u32x4 v[N];
 #pragma unroll
   for (int u = 0; u < N; ++u) {
-    const int e = u * kPackBlock + tid;
+    const uint32_t e = u * 64 + lane;
     v[u] = load16(src + (size_t)(kWhole ? e : min(e, n - 1)) * 16);
   }
 #pragma unroll
   for (int u = 0; u < N; ++u) {
-    const int e = u * kPackBlock + tid;
+    const uint32_t e = u * 64 + lane;
     if (kWhole || e < n) store16(dst + (size_t)e * 16, v[u]);
   }
 }
 
+// A piece of the work list, by wave-uniform loads.
+__device__ __forceinline__ MigratePiece ld_piece(const uint8_t* p) {
+  return MigratePiece{ld<true, uint64_t>(p + offsetof(MigratePiece, src)),
+                      ld<true, uint64_t>(p + offsetof(MigratePiece, dst)),
+                      ld<true, uint32_t>(p + offsetof(MigratePiece, vecs)), 0, 0};
+}
+
 // Tier migration (Sec. 3.2): workgroups [0, n_lists) each put one sample's new
-// page list into the arena and its place into the descriptor; a few others
-// walk the pages in steps of kMigrateVecs vectors, reading or writing the host
-// tier's memory directly.
+// page list into the arena and its place into the descriptor; the waves of a
+// few others walk the pieces in steps of kMigrateVecs vectors, reading or
+// writing the host tier's memory directly.
 //
 // The link to the host bounds it, and all it needs of the chip is enough bytes
-// in flight to cover the link's latency. 97 MB to the host tier take 1.69 ms
-// (57 GB/s, the rate of one large copy) with 16 workgroups of 16 KiB each. The
-// other way 16 read as fast, but a read across the link holds up the loads of
-// the packs that share its CU: beside a stream of packs of 35.4 us each, the
-// packs take 37.9, 39.3, 41.5 and 48 us with 8, 12, 16 and 24 workgroups and
-// the migration 2.65, 2.27, 2.07 and 1.9 ms. As copies by the DMA engines,
-// one per run of adjacent pages, both directions took 2.7 ms and the packs
-// beside them 37.3 us.
+// in flight to cover the link's latency: 57 GB/s (the rate of one large copy)
+// with 40 waves of 4 KiB each to HBM, 64 to the host tier. To keep them in
+// flight whatever the pages' size, adjacent small pages are cut into whole
+// steps and a piece's place in the work list, itself across the link, is read a
+// step ahead: 33.6 MB of adjacent 8 KiB pages take 755 us to HBM and 750 to the
+// host tier, of 128 KiB pages 616 and 614; with one page a step, its place read
+// in front of it, 1372 and 864, 760 and 638 (as one DMA copy per adjacent run
+// 770 and 788, 735 and 740).
+//
+// A read across the link holds up the loads of the packs that share its CU:
+// beside a stream of packs of 35.4 us each, the packs take 37.9, 39.3, 41.5 and
+// 48 us with 8, 12, 16 and 24 workgroups and the migration of 97 MB 2.65, 2.27,
+// 2.07 and 1.9 ms.
 __global__ __launch_bounds__(kPackBlock) void k_migrate(MigrateArgs a) {
   const int tid = threadIdx.x;
-  const uint8_t* pages = a.stage;
   if ((int)blockIdx.x < a.n_lists) {
-    const uint8_t* l = a.stage + sizeof(MigratePage) * (size_t)a.n_pages + sizeof(MigrateList) * (size_t)blockIdx.x;
+    const uint8_t* l = a.stage + sizeof(MigrateList) * (size_t)blockIdx.x;
     const int64_t words_at = ld<true, int64_t>(l + offsetof(MigrateList, words_at));
     const int64_t meta_off = ld<true, int64_t>(l + offsetof(MigrateList, meta_off));
     const int32_t n_words = ld<true, int32_t>(l + offsetof(MigrateList, n_words));
@@ -531,25 +542,40 @@ __global__ __launch_bounds__(kPackBlock) void k_migrate(MigrateArgs a) {
     if (tid == 0) a.desc_table[slot].page_off = meta_off;
     return;
   }
-  const int64_t first = (int64_t)blockIdx.x - a.n_lists;
-  const int64_t grid = (int64_t)gridDim.x - a.n_lists;
-  const int64_t page_stride = grid / a.steps_per_page, step_stride = grid % a.steps_per_page;
-  int64_t page = first / a.steps_per_page, step = first % a.steps_per_page;
-  while (page < a.n_pages) {
-    const uint8_t* e = pages + sizeof(MigratePage) * (size_t)page;
-    const uint64_t src = ld<true, uint64_t>(e + offsetof(MigratePage, src));
-    const uint64_t dst = ld<true, uint64_t>(e + offsetof(MigratePage, dst));
-    const int64_t left = ld<true, int64_t>(e + offsetof(MigratePage, vecs)) - step * kMigrateVecs;
-    const uint8_t* from = reinterpret_cast<const uint8_t*>(src) + step * kMigrateVecs * 16;
-    uint8_t* to = reinterpret_cast<uint8_t*>(dst) + step * kMigrateVecs * 16;
-    if (left >= kMigrateVecs) migrate_step<true>(from, to, kMigrateVecs, tid);
-    else if (left > 0) migrate_step<false>(from, to, (int)left, tid);
-    page += page_stride;
-    step += step_stride;
-    if (step >= a.steps_per_page) {
-      step -= a.steps_per_page;
-      ++page;
+  constexpr int kWaves = kPackBlock / 64;
+  const uint32_t lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint8_t* pieces = a.stage + a.pieces_at;
+  const uint32_t first = (blockIdx.x - (uint32_t)a.n_lists) * kWaves + (uint32_t)wave;
+  const uint32_t stride = (gridDim.x - (uint32_t)a.n_lists) * kWaves;
+  const uint32_t piece_stride = stride / a.steps_per_piece, step_stride = stride % a.steps_per_piece;
+  uint32_t piece = first / a.steps_per_piece, step = first % a.steps_per_piece;
+  if (piece >= a.n_pieces) return;
+  MigratePiece cur = ld_piece(pieces + sizeof(MigratePiece) * (size_t)piece);
+  // Waited for here: the first step's wait would otherwise be placed behind the
+  // next piece's load and wait for that one too, in every step.
+  asm volatile("" : : "s"(cur.src), "s"(cur.dst), "s"(cur.vecs));
+  for (;;) {
+    uint32_t next = piece + piece_stride, next_step = step + step_stride;
+    if (next_step >= a.steps_per_piece) {
+      next_step -= a.steps_per_piece;
+      ++next;
     }
+    // The next piece's place, in flight while this step's vectors are.
+    MigratePiece then = cur;
+    if (next < a.n_pieces) then = ld_piece(pieces + sizeof(MigratePiece) * (size_t)next);
+    const uint32_t done = step * kMigrateVecs;
+    if (cur.vecs > done) {
+      const uint32_t n = cur.vecs - done;
+      const uint8_t* from = reinterpret_cast<const uint8_t*>(cur.src) + (uint64_t)done * 16;
+      uint8_t* to = reinterpret_cast<uint8_t*>(cur.dst) + (uint64_t)done * 16;
+      if (n >= kMigrateVecs) migrate_step<true>(from, to, kMigrateVecs, lane);
+      else migrate_step<false>(from, to, n, lane);
+    }
+    if (next >= a.n_pieces) return;
+    piece = next;
+    step = next_step;
+    cur = then;
   }
 }
 
@@ -758,8 +784,9 @@ hipError_t launch_write(const WritePlan& w, int n_cu, hipStream_t stream, hipEve
 }
 
 hipError_t launch_migrate(const MigrateArgs& a, hipStream_t stream, hipEvent_t done) {
-  const int64_t steps = a.n_pages * a.steps_per_page;
-  const int grid = a.n_lists + (int)std::min<int64_t>(steps, kMigrateGrid[a.tier]);
+  constexpr int kWaves = kPackBlock / 64;
+  const int64_t wgs = ((int64_t)a.n_pieces * a.steps_per_piece + kWaves - 1) / kWaves;
+  const int grid = a.n_lists + (int)std::min<int64_t>(wgs, kMigrateGrid[a.tier]);
   return launch(&k_migrate, grid, kPackBlock, 0, stream, done, a);
 }
 

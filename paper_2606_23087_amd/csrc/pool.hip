@@ -1130,11 +1130,16 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
       unreserve();
       return st;
     }
-    // Staging: the work list of the migration kernel (pages, then the samples'
-    // new page lists).
-    size_t at = sizeof(fp::MigratePage) * (size_t)need + sizeof(fp::MigrateList) * recs.size();
-    size_t stage_bytes = at;
-    for (SampleRec* r : recs) stage_bytes += (size_t)align16(8 * (int64_t)r->pages.size());
+    // Staging: the work list of the migration kernel (the samples' new page
+    // lists, then the pieces to copy, of at most `most` vectors each).
+    const int64_t page_vecs = p->pb / 16;
+    const int64_t most = page_vecs < fp::kMigratePageSteps * (int64_t)fp::kMigrateVecs
+                             ? (int64_t)fp::kMigrateVecs
+                             : std::min(page_vecs, fp::kMigratePieceVecs);
+    size_t at = sizeof(fp::MigrateList) * recs.size();
+    size_t pieces_at = at;
+    for (SampleRec* r : recs) pieces_at += (size_t)align16(8 * (int64_t)r->pages.size());
+    const size_t stage_bytes = pieces_at + sizeof(fp::MigratePiece) * (size_t)(need * ((page_vecs + most - 1) / most));
     Stage* sg = nullptr;
     st = stage_acquire(p, stage_bytes, 0, &sg);
     int32_t ev = -1;
@@ -1148,8 +1153,27 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
     std::vector<std::vector<uint64_t>> old_pages(recs.size());
     const int64_t P = p->cfg.page_tokens;
     auto frame = [&](uint64_t gva) { return p->pte[(size_t)page_number(p, gva)] & fp::PTE_ADDR_MASK; };
-    fp::MigratePage* entry = reinterpret_cast<fp::MigratePage*>(sg->host);
-    fp::MigrateList* list = reinterpret_cast<fp::MigrateList*>(sg->host + sizeof(fp::MigratePage) * (size_t)need);
+    fp::MigrateList* list = reinterpret_cast<fp::MigrateList*>(sg->host);
+    fp::MigratePiece* const pieces = reinterpret_cast<fp::MigratePiece*>(sg->host + pieces_at);
+    int64_t n_pieces = 0;
+    // Copies are added in page order; what continues the last piece on both
+    // sides fills it up first (so no more pieces come of it than of each page
+    // on its own).
+    auto add_copy = [&](uint64_t src, uint64_t dst, int64_t vecs) {
+      if (n_pieces > 0) {
+        fp::MigratePiece& last = pieces[n_pieces - 1];
+        const uint64_t done = 16 * (uint64_t)last.vecs;
+        if (last.src + done == src && last.dst + done == dst) {
+          const int64_t more = std::min(vecs, most - (int64_t)last.vecs);
+          last.vecs += (uint32_t)more;
+          src += 16 * (uint64_t)more;
+          dst += 16 * (uint64_t)more;
+          vecs -= more;
+        }
+      }
+      for (; vecs > 0; vecs -= most, src += 16 * (uint64_t)most, dst += 16 * (uint64_t)most)
+        pieces[n_pieces++] = fp::MigratePiece{src, dst, (uint32_t)std::min(vecs, most), 0, 0};
+    };
     for (size_t j = 0; j < recs.size(); ++j) {
       SampleRec& r = *recs[j];
       new_pages[j] = r.pages;
@@ -1160,7 +1184,7 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
         p->n_free[tier] -= 1;
         const uint64_t gva = p->page_gva(tier, i);
         const int64_t rows = std::min<int64_t>(P, r.n_vis - (int64_t)k * P);
-        *entry++ = fp::MigratePage{frame(r.pages[(size_t)k]), frame(gva), rows * (p->rb / 16), 0};
+        add_copy(frame(r.pages[(size_t)k]), frame(gva), rows * (p->rb / 16));
         old_pages[j].push_back(r.pages[(size_t)k]);
         new_pages[j][(size_t)k] = gva;
       }
@@ -1172,8 +1196,9 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
     ma.stage = sg->host_dev;
     ma.meta = p->meta_dev;
     ma.desc_table = p->desc_dev;
-    ma.n_pages = need;
-    ma.steps_per_page = (p->pb / 16 + fp::kMigrateVecs - 1) / fp::kMigrateVecs;
+    ma.pieces_at = (int64_t)pieces_at;
+    ma.n_pieces = (uint32_t)n_pieces;
+    ma.steps_per_piece = (uint32_t)((most + fp::kMigrateVecs - 1) / fp::kMigrateVecs);
     ma.n_lists = (int32_t)recs.size();
     ma.tier = tier;
     const hipError_t e = fp::launch_migrate(ma, hs, p->events.ev[(size_t)ev]);

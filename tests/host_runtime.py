@@ -54,29 +54,32 @@ def build(tmp, csrc=CSRC):
         f = getattr(lib, name)
         f.restype, f.argtypes = res, args
     lib.stub_log.restype = C.c_char_p
+    lib.stub_migrate_args.restype = C.c_void_p
     return lib
 
 
 class Pool:
-    """A pool of a host build. Sizes: 64-byte rows, pages of 4 rows, scatter policy, both tiers."""
+    """A pool of a host build: both tiers, scatter policy, 64-byte rows and pages of 4 rows unless said otherwise."""
 
-    def __init__(self, lib, hbm_pages=64, host_pages=64):
-        self.lib = lib
+    def __init__(self, lib, hbm_pages=64, host_pages=64, hidden=32, page=4, chunk_bytes=0, shuffle=0):
+        self.lib, self.page = lib, page
         cfg = fp.fp_pool_config()
         lib.fp_config_init(C.byref(cfg))
-        cfg.hidden, cfg.page_tokens, cfg.vocab = 32, 4, 100
+        cfg.hidden, cfg.page_tokens, cfg.vocab = hidden, page, 100
         cfg.hbm_pages, cfg.host_pages = hbm_pages, host_pages
+        cfg.chunk_bytes, cfg.frame_shuffle_seed = chunk_bytes, shuffle
         cfg.alloc_policy = fp.FP_ALLOC_SCATTER
         self.p = C.c_void_p()
         assert lib.pool_create(C.byref(cfg), C.byref(self.p)) == 0, lib.fp_last_error()
 
-    def write(self, n_text, rows, stream, tier=0):
-        """(status, id)"""
+    def write(self, n_text, rows, stream, tiers=(0,)):
+        """(status, id); the wished tiers of the pages are `tiers`, repeated."""
         text = (C.c_int32 * max(n_text, 1))()
         one = (C.c_int32 * 1)(0)
         ntok = (C.c_int32 * 1)(rows)
-        wish = (C.c_uint8 * max(-(-rows // 4), 1))(*([tier] * max(-(-rows // 4), 1)))
-        vis = np.zeros((max(rows, 1), 32), np.int16)
+        n = -(-rows // self.page)
+        wish = (C.c_uint8 * max(n, 1))(*[tiers[k % len(tiers)] for k in range(n)])
+        vis = np.zeros(64, np.int16)
         sid = C.c_uint64()
         st = self.lib.pool_write_sample(self.p, text, n_text, one, ntok, 1, C.c_void_p(_aligned(vis)), wish, stream, sid)
         return st, sid.value
@@ -106,9 +109,18 @@ class Pool:
 
     def pages(self, i):
         n = C.c_int32()
-        buf = (C.c_uint64 * 256)()
-        assert self.lib.pool_sample_pages(self.p, i, buf, 256, n) == 0
+        buf = (C.c_uint64 * 4096)()
+        assert self.lib.pool_sample_pages(self.p, i, buf, 4096, n) == 0
         return list(buf[:n.value])
+
+    def frames(self, i):
+        """(tier, address) of each of a sample's pages."""
+        out = []
+        for g in self.pages(i):
+            t, at = C.c_int32(), C.c_uint64()
+            assert self.lib.pool_translate(self.p, g, t, at) == 0
+            out.append((t.value, at.value))
+        return out
 
     def destroy(self):
         assert self.lib.pool_destroy(self.p) == 0

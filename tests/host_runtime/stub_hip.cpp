@@ -13,6 +13,7 @@
 
 namespace {
 
+constexpr size_t kMigrateArgs = 48;
 std::string g_log;
 hipError_t g_pending = hipSuccess;    // what hipGetLastError would return
 hipError_t g_launch = hipSuccess;     // status of the next launches
@@ -21,6 +22,7 @@ hipError_t g_wait = hipSuccess;       // status of the next stream waits
 bool g_busy = false;                  // streams and events have not finished
 bool g_capturing = false;
 int g_events = 0;
+unsigned char g_migrate[64];          // the arguments of the last migration kernel
 
 // Kernel names by handle; built on first use, as the library's objects register theirs while it is loaded.
 std::map<const void*, std::string>& kernels() {
@@ -41,10 +43,11 @@ void note(const char* what, T* on) {
   g_log += '\n';
 }
 
-hipError_t launched(const void* f, hipStream_t s) {
+hipError_t launched(const void* f, void** args, hipStream_t s) {
   auto it = kernels().find(f);
   const std::string what = "launch " + (it == kernels().end() ? std::string("?") : it->second);
   note(what.c_str(), s);
+  if (what.find("k_migrate") != std::string::npos) std::memcpy(g_migrate, args[0], kMigrateArgs);
   return done(g_launch);
 }
 
@@ -70,6 +73,7 @@ void stub_launch(int e) { g_launch = (hipError_t)e; }
 void stub_record(int e) { g_record = (hipError_t)e; }
 void stub_wait(int e) { g_wait = (hipError_t)e; }
 void stub_busy(int b) { g_busy = b != 0; }
+const void* stub_migrate_args() { return g_migrate; }
 void stub_capturing(int c) { g_capturing = c != 0; }
 
 // Registration of the compiled kernels and device variables.
@@ -145,9 +149,10 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
   return hipSuccess;
 }
 
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t s) { return launched(f, s); }
-hipError_t hipExtLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t s, hipEvent_t, hipEvent_t, int) {
-  return launched(f, s);
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** a, size_t, hipStream_t s) { return launched(f, a, s); }
+hipError_t hipExtLaunchKernel(const void* f, dim3, dim3, void** a, size_t, hipStream_t s, hipEvent_t, hipEvent_t,
+                              int) {
+  return launched(f, a, s);
 }
 
 }  // extern "C"
