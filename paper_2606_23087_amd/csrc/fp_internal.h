@@ -213,9 +213,10 @@ struct alignas(16) MigratePiece {
   uint32_t pad;
   uint64_t pad1;
 };
-// Workgroups that copy pieces, by the target tier, and vectors of a piece a
-// wave moves per step (see k_migrate).
-constexpr int kMigrateGrid[2] = {10, 16};
+// Threads of a workgroup (one wave), workgroups that copy pieces, by the target
+// tier, and vectors of a piece one moves per step (see k_migrate).
+constexpr int kMigrateBlock = 64;
+constexpr int kMigrateGrid[2] = {21, 40};
 constexpr uint32_t kMigrateVecs = 64 * 4;
 constexpr int64_t kMigratePieceVecs = 1 << 30;
 // A page of at least this many steps is a piece of its own, of which at most

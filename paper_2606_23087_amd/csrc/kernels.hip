@@ -29,6 +29,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // (vector memory counter only) instead of flat loads, which also count
 // against the LDS counter and force the compiler to wait for each one.
 typedef __attribute__((address_space(1))) const u32x4 g_u32x4_c;
+typedef __attribute__((address_space(1))) u32x4 g_u32x4;
 
 __device__ __forceinline__ u32x4 load16(const uint8_t* p) {
   return __builtin_nontemporal_load((g_u32x4_c*)p);
@@ -486,8 +487,10 @@ __global__ __launch_bounds__(kPackBlock) void k_write(int32_t g0, int32_t g1, in
 }
 
 // One step of a migration, by one wave: n vectors of a piece (at most
-// kMigrateVecs). kWhole as in write_chunk.
-template <bool kWhole>
+// kMigrateVecs). kWhole as in write_chunk. Stores to HBM are the compiler's own:
+// it does not see those of an asm block, so that its wait for a load issued
+// before them waits for them as well.
+template <bool kWhole, bool kToHost>
 __device__ __forceinline__ void migrate_step(const uint8_t* src, uint8_t* dst, uint32_t n, uint32_t lane) {
   constexpr int N = kMigrateVecs / 64;
   u32x4 v[N];
@@ -499,8 +502,12 @@ __device__ __forceinline__ void migrate_step(const uint8_t* src, uint8_t* dst, u
 #pragma unroll
   for (int u = 0; u < N; ++u) {
     const uint32_t e = u * 64 + lane;
-    if (kWhole || e < n) store16(dst + (size_t)e * 16, v[u]);
+    if (kWhole || e < n) {
+      if constexpr (kToHost) store16(dst + (size_t)e * 16, v[u]);
+      else __builtin_nontemporal_store(v[u], (g_u32x4*)(dst + (size_t)e * 16));
+    }
   }
+  if constexpr (kWhole) asm volatile(";; whole step");   // keeps the two forms' last stores, and their waits, apart
 }
 
 // A piece of the work list, by wave-uniform loads.
@@ -511,43 +518,53 @@ __device__ __forceinline__ MigratePiece ld_piece(const uint8_t* p) {
 }
 
 // Tier migration (Sec. 3.2): workgroups [0, n_lists) each put one sample's new
-// page list into the arena and its place into the descriptor; the waves of a
-// few others walk the pieces in steps of kMigrateVecs vectors, reading or
-// writing the host tier's memory directly.
+// page list into the arena and its place into the descriptor; a few others walk
+// the pieces in steps of kMigrateVecs vectors, reading or writing the host
+// tier's memory directly. A workgroup is one wave.
 //
 // The link to the host bounds it, and all it needs of the chip is enough bytes
-// in flight to cover the link's latency: 57 GB/s (the rate of one large copy)
-// with 40 waves of 4 KiB each to HBM, 64 to the host tier. To keep them in
-// flight whatever the pages' size, adjacent small pages are cut into whole
-// steps and a piece's place in the work list, itself across the link, is read a
-// step ahead: 33.6 MB of adjacent 8 KiB pages take 755 us to HBM and 750 to the
-// host tier, of 128 KiB pages 616 and 614; with one page a step, its place read
-// in front of it, 1372 and 864, 760 and 638 (as one DMA copy per adjacent run
-// 770 and 788, 735 and 740).
+// in flight to cover the link's latency: 57 GB/s is the rate of one large copy.
+// To keep them in flight whatever the pages' size, adjacent small pages are cut
+// into whole steps and a piece's place in the work list, itself across the link,
+// is read a step ahead: 33.6 MB of adjacent 8 KiB pages take 773 us to HBM and
+// 753 to the host tier, of 512 KiB pages 623 and 614; with one page a step, its
+// place read in front of it, 1372 and 864, 645 and 611 (as one DMA copy per
+// adjacent run 770 and 788, 730 and 739).
 //
-// A read across the link holds up the loads of the packs that share its CU:
-// beside a stream of packs of 35.4 us each, the packs take 37.9, 39.3, 41.5 and
-// 48 us with 8, 12, 16 and 24 workgroups and the migration of 97 MB 2.65, 2.27,
-// 2.07 and 1.9 ms.
-__global__ __launch_bounds__(kPackBlock) void k_migrate(MigrateArgs a) {
-  const int tid = threadIdx.x;
+// What packs beside it lose decides the shape. A CU returns its loads in order,
+// so a read across the link holds up the packs' loads there: single waves spread
+// over more CUs cost the packs less than as many in groups of four, and waves
+// that do not wait for their stores are fewer. (To the host tier they do wait, as
+// a side effect of store16; stores without its sc1 bit gather in the L2 and then hold up
+// all traffic: packs 60 us.) 194 MB of scattered 512 KiB pages beside packs of 235
+// MB (38.0 us alone), the packs / the migration / the migration alone:
+//   to HBM    16 waves 40.7 us, 6.4 ms, 4.3   21 waves 41.2, 5.0, 3.51   26 waves 42.0, 4.2, 3.49
+//             10 groups of 4, waiting for their stores 41.4, 7.3, 3.57   as DMA copies 39.9, 7.8, 7.3
+//   to host   36 waves 39.6, 5.6, 3.50   40 waves 39.9, 5.1, 3.47   48 waves 40.6, 4.5, 3.46
+//             16 groups of 4 40.1, 4.8, 3.45   as DMA copies 39.7, 7.8, 7.3
+// To HBM the packs lose as much to a migration as to its DMA copies (their delay
+// times its duration), to the host tier three quarters of that.
+template <bool kToHost>
+__global__ __launch_bounds__(kMigrateBlock) void k_migrate(MigrateArgs a) {
+  const uint32_t lane = threadIdx.x;
   if ((int)blockIdx.x < a.n_lists) {
     const uint8_t* l = a.stage + sizeof(MigrateList) * (size_t)blockIdx.x;
     const int64_t words_at = ld<true, int64_t>(l + offsetof(MigrateList, words_at));
     const int64_t meta_off = ld<true, int64_t>(l + offsetof(MigrateList, meta_off));
     const int32_t n_words = ld<true, int32_t>(l + offsetof(MigrateList, n_words));
     const int32_t slot = ld<true, int32_t>(l + offsetof(MigrateList, slot));
-    uint64_t* to = reinterpret_cast<uint64_t*>(a.meta + meta_off);
-    for (int i = tid; i < n_words; i += kPackBlock) to[i] = ld<false, uint64_t>(a.stage + words_at + 8 * (int64_t)i);
-    if (tid == 0) a.desc_table[slot].page_off = meta_off;
+    // Two words a vector: both ends have room for the one past an odd number.
+    const uint32_t vecs = ((uint32_t)n_words + 1) / 2;
+    const uint8_t* from = a.stage + words_at;
+    uint8_t* to = a.meta + meta_off;
+    for (uint32_t v = 0; v < vecs; v += kMigrateVecs)
+      migrate_step<false, false>(from + (size_t)v * 16, to + (size_t)v * 16, min(vecs - v, kMigrateVecs), lane);
+    if (lane == 0) a.desc_table[slot].page_off = meta_off;
     return;
   }
-  constexpr int kWaves = kPackBlock / 64;
-  const uint32_t lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint8_t* pieces = a.stage + a.pieces_at;
-  const uint32_t first = (blockIdx.x - (uint32_t)a.n_lists) * kWaves + (uint32_t)wave;
-  const uint32_t stride = (gridDim.x - (uint32_t)a.n_lists) * kWaves;
+  const uint32_t first = blockIdx.x - (uint32_t)a.n_lists;
+  const uint32_t stride = gridDim.x - (uint32_t)a.n_lists;
   const uint32_t piece_stride = stride / a.steps_per_piece, step_stride = stride % a.steps_per_piece;
   uint32_t piece = first / a.steps_per_piece, step = first % a.steps_per_piece;
   if (piece >= a.n_pieces) return;
@@ -569,8 +586,8 @@ __global__ __launch_bounds__(kPackBlock) void k_migrate(MigrateArgs a) {
       const uint32_t n = cur.vecs - done;
       const uint8_t* from = reinterpret_cast<const uint8_t*>(cur.src) + (uint64_t)done * 16;
       uint8_t* to = reinterpret_cast<uint8_t*>(cur.dst) + (uint64_t)done * 16;
-      if (n >= kMigrateVecs) migrate_step<true>(from, to, kMigrateVecs, lane);
-      else migrate_step<false>(from, to, n, lane);
+      if (n >= kMigrateVecs) migrate_step<true, kToHost>(from, to, kMigrateVecs, lane);
+      else migrate_step<false, kToHost>(from, to, n, lane);
     }
     if (next >= a.n_pieces) return;
     piece = next;
@@ -595,8 +612,8 @@ struct As {
   using type = T;
 };
 
-// Launches a kernel of kPackBlock or kBlock threads a workgroup; `done`, if
-// not null, completes with it. The status is the launch's own: the thread's
+// Launches a kernel of `block` threads a workgroup; `done`, if not null,
+// completes with it. The status is the launch's own: the thread's
 // last error (hipGetLastError) may be an earlier call's, of this library or of
 // the caller, and the kernel is queued all the same.
 // An event recorded after a kernel costs the stream about 3 us; a launch's own
@@ -784,10 +801,9 @@ hipError_t launch_write(const WritePlan& w, int n_cu, hipStream_t stream, hipEve
 }
 
 hipError_t launch_migrate(const MigrateArgs& a, hipStream_t stream, hipEvent_t done) {
-  constexpr int kWaves = kPackBlock / 64;
-  const int64_t wgs = ((int64_t)a.n_pieces * a.steps_per_piece + kWaves - 1) / kWaves;
-  const int grid = a.n_lists + (int)std::min<int64_t>(wgs, kMigrateGrid[a.tier]);
-  return launch(&k_migrate, grid, kPackBlock, 0, stream, done, a);
+  const int64_t steps = (int64_t)a.n_pieces * a.steps_per_piece;
+  const int grid = a.n_lists + (int)std::min<int64_t>(steps, kMigrateGrid[a.tier]);
+  return launch(a.tier ? &k_migrate<true> : &k_migrate<false>, grid, kMigrateBlock, 0, stream, done, a);
 }
 
 Divisors make_divisors(int64_t row_bytes, int64_t page_tokens, uint64_t page_bytes) {
