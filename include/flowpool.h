@@ -221,7 +221,8 @@ fp_status pool_reclaim(fp_pool* p, int32_t wait, int64_t* out_deferred_pages);
  * taking the next page of the tier's free stack, so a sample's GVAs change
  * and its bytes do not. One kernel on `stream`, of a few workgroups that
  * read or write the host tier's memory across the link, copies the pages and
- * uploads the samples' new page lists. Packs and plans
+ * uploads the samples' new page lists; runs of 8 MiB or more of pages adjacent
+ * in both tiers are copies by the DMA engines ahead of it. Packs and plans
  * enqueued later on other streams wait for them; packs enqueued earlier keep
  * reading the old pages, which return to their tier's free stack
  * (last-page-first) once the copies and those packs have completed. Used to

@@ -224,6 +224,15 @@ constexpr int64_t kMigratePieceVecs = 1 << 30;
 // both tiers are taken together and cut into pieces of one step.
 constexpr int kMigratePageSteps = 8;
 
+// A run of adjacent pages of at least this many bytes is one copy by the DMA
+// engines instead, which leave the CUs to the packs beside them but take some 10
+// us a copy. 134 MB to HBM / to the host tier, by copies and by the kernel: in
+// runs of 8 MiB 2.52 / 2.53 and 2.42 / 2.39 ms alone, 2.75 / 2.55 and 3.44 / 3.52
+// beside a stream of packs (38.7 / 38.5 us each and 39.0 / 38.6); in runs of 32 MiB
+// 2.40 / 2.41 and 2.40 / 2.38 alone, 2.41 / 2.42 and 3.44 / 3.55 beside packs. In
+// runs of 4 MiB copies would take 17 % longer alone and gain 4 % beside packs.
+constexpr int64_t kMigrateCopyBytes = 8 << 20;
+
 struct MigrateArgs {
   const uint8_t* stage;       // n_lists MigrateList, the lists' words, n_pieces MigratePiece
   uint8_t* meta;

@@ -268,6 +268,7 @@ struct fp_pool {
   uint64_t max_size[2] = {0, 0};
   // physical backing
   std::vector<void*> chunks[2];
+  std::unordered_set<uint64_t> chunk_starts;   // addresses of the chunks of both tiers
   int64_t frames_per_chunk[2] = {1, 1};
   bool owned[2] = {true, true};       // false: the caller's backing, never freed here
   std::vector<uint64_t> pte;          // host mirror, index = global vpn
@@ -760,6 +761,8 @@ fp_status pool_create(const fp_pool_config* cfg_in, fp_pool** out) {
         p->chunks[t].push_back(ptr);
       }
     }
+    for (const auto& tier_chunks : p->chunks)
+      for (void* c : tier_chunks) p->chunk_starts.insert((uint64_t)c);
     // Page table: GVA page (HBM pages, then host pages) -> physical frame.
     const int64_t total = p->n_pages[0] + p->n_pages[1];
     p->pte.resize((size_t)total);
@@ -1148,31 +1151,28 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
       unreserve();
       return st;
     }
-    // From here on nothing fails half-way but the launch: take the pages.
+    // From here on nothing fails half-way but a copy or the launch: take the pages.
     std::vector<std::vector<uint64_t>> new_pages(recs.size());
     std::vector<std::vector<uint64_t>> old_pages(recs.size());
     const int64_t P = p->cfg.page_tokens;
     auto frame = [&](uint64_t gva) { return p->pte[(size_t)page_number(p, gva)] & fp::PTE_ADDR_MASK; };
     fp::MigrateList* list = reinterpret_cast<fp::MigrateList*>(sg->host);
     fp::MigratePiece* const pieces = reinterpret_cast<fp::MigratePiece*>(sg->host + pieces_at);
-    int64_t n_pieces = 0;
-    // Copies are added in page order; what continues the last piece on both
-    // sides fills it up first (so no more pieces come of it than of each page
-    // on its own).
+    // Runs of pages that are adjacent in both tiers, each inside one backing
+    // chunk (one allocation) on either side.
+    struct Run { uint64_t src, dst; int64_t vecs; };
+    std::vector<Run> runs;
     auto add_copy = [&](uint64_t src, uint64_t dst, int64_t vecs) {
-      if (n_pieces > 0) {
-        fp::MigratePiece& last = pieces[n_pieces - 1];
+      if (!runs.empty()) {
+        Run& last = runs.back();
         const uint64_t done = 16 * (uint64_t)last.vecs;
-        if (last.src + done == src && last.dst + done == dst) {
-          const int64_t more = std::min(vecs, most - (int64_t)last.vecs);
-          last.vecs += (uint32_t)more;
-          src += 16 * (uint64_t)more;
-          dst += 16 * (uint64_t)more;
-          vecs -= more;
+        if (last.src + done == src && last.dst + done == dst && !p->chunk_starts.count(src) &&
+            !p->chunk_starts.count(dst)) {
+          last.vecs += vecs;
+          return;
         }
       }
-      for (; vecs > 0; vecs -= most, src += 16 * (uint64_t)most, dst += 16 * (uint64_t)most)
-        pieces[n_pieces++] = fp::MigratePiece{src, dst, (uint32_t)std::min(vecs, most), 0, 0};
+      runs.push_back(Run{src, dst, vecs});
     };
     for (size_t j = 0; j < recs.size(); ++j) {
       SampleRec& r = *recs[j];
@@ -1197,13 +1197,27 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
     ma.meta = p->meta_dev;
     ma.desc_table = p->desc_dev;
     ma.pieces_at = (int64_t)pieces_at;
-    ma.n_pieces = (uint32_t)n_pieces;
+    // A long run is one copy by the DMA engines, the others are cut into the
+    // kernel's pieces (no more of them than of each page on its own).
+    hipError_t e = hipSuccess;
+    uint32_t n_pieces = 0;
+    for (const Run& run : runs) {
+      if (16 * run.vecs >= fp::kMigrateCopyBytes) {
+        e = hipMemcpyAsync((void*)run.dst, (const void*)run.src, 16 * (size_t)run.vecs, hipMemcpyDefault, hs);
+        if (e != hipSuccess) break;
+        continue;
+      }
+      for (int64_t v = 0; v < run.vecs; v += most)
+        pieces[n_pieces++] = fp::MigratePiece{run.src + 16 * (uint64_t)v, run.dst + 16 * (uint64_t)v,
+                                              (uint32_t)std::min(run.vecs - v, most), 0, 0};
+    }
+    ma.n_pieces = n_pieces;
     ma.steps_per_piece = (uint32_t)((most + fp::kMigrateVecs - 1) / fp::kMigrateVecs);
     ma.n_lists = (int32_t)recs.size();
     ma.tier = tier;
-    const hipError_t e = fp::launch_migrate(ma, hs, p->events.ev[(size_t)ev]);
+    if (e == hipSuccess) e = fp::launch_migrate(ma, hs, p->events.ev[(size_t)ev]);
     if (e != hipSuccess) {
-      st = fail_behind(hs, fail(FP_EHIP, "migration kernel: %s", hipGetErrorString(e)));
+      st = fail_behind(hs, fail(FP_EHIP, "migration: %s", hipGetErrorString(e)));
       p->events.unref(ev);
       for (size_t j = 0; j < recs.size(); ++j) {
         std::vector<uint64_t> taken;

@@ -125,6 +125,12 @@ class Pool:
     def destroy(self):
         assert self.lib.pool_destroy(self.p) == 0
 
+    def copies(self):
+        """(source, destination, bytes) of the asynchronous copies since the last call of log."""
+        at = C.POINTER(C.c_ulonglong)()
+        n = self.lib.stub_copies(C.byref(at))
+        return [(at[3 * k], at[3 * k + 1], at[3 * k + 2]) for k in range(n)]
+
     def log(self):
         """Lines logged since the last call."""
         l = self.lib.stub_log().decode().split("\n")[:-1]

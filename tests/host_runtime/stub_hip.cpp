@@ -10,6 +10,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <vector>
 
 namespace {
 
@@ -22,6 +23,8 @@ hipError_t g_wait = hipSuccess;       // status of the next stream waits
 bool g_busy = false;                  // streams and events have not finished
 bool g_capturing = false;
 int g_events = 0;
+hipError_t g_copy = hipSuccess;       // status of the next asynchronous copies
+std::vector<unsigned long long> g_copies;   // source, destination and bytes of each since stub_clear
 unsigned char g_migrate[64];          // the arguments of the last migration kernel
 
 // Kernel names by handle; built on first use, as the library's objects register theirs while it is loaded.
@@ -66,7 +69,15 @@ extern "C" {
 
 // What the tests call.
 const char* stub_log() { return g_log.c_str(); }
-void stub_clear() { g_log.clear(); }
+void stub_clear() {
+  g_log.clear();
+  g_copies.clear();
+}
+void stub_copy(int e) { g_copy = (hipError_t)e; }
+int stub_copies(const unsigned long long** at) {
+  *at = g_copies.data();
+  return (int)(g_copies.size() / 3);
+}
 void stub_pending(int e) { g_pending = (hipError_t)e; }
 int stub_peek() { return (int)g_pending; }
 void stub_launch(int e) { g_launch = (hipError_t)e; }
@@ -129,8 +140,9 @@ hipError_t hipGetSymbolAddress(void** p, const void*) {
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
   note("copy", st);
-  std::memcpy(d, s, n);
-  return hipSuccess;
+  g_copies.insert(g_copies.end(), {(unsigned long long)(uintptr_t)s, (unsigned long long)(uintptr_t)d, n});
+  if (done(g_copy) == hipSuccess) std::memcpy(d, s, n);
+  return g_copy;
 }
 
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {

@@ -2,7 +2,9 @@
 host_runtime.py): whatever the page size, the order of the free pages, partly
 migrated samples and partial last pages, its pieces copy each moved page's rows
 to its new frame once, no piece is longer than the kernel's steps for one, and
-the list stays inside the staging buffer.
+the list stays inside the staging buffer. Runs of 8 MiB of adjacent pages or
+more, and only those, are copies by the runtime, none across two chunks of a
+tier's backing.
 """
 
 import ctypes as C
@@ -68,6 +70,7 @@ def test_work_list_copies_what_moved(lib, hidden, page, shuffle, chunk_pages):
         before = {i: pool.frames(i) for i, _ in some}
         lib.stub_clear()
         assert pool.migrate([i for i, _ in some], tier, S1) == 0
+        copies = pool.copies()
         log = pool.log()
         after = {i: pool.frames(i) for i, _ in some}
         want, moved = [], 0
@@ -80,6 +83,7 @@ def test_work_list_copies_what_moved(lib, hidden, page, shuffle, chunk_pages):
         if not moved:
             assert not any("launch" in l for l in log)
             continue
+        assert not copies
         pieces, lists, steps, to, used = work_list(lib)
         assert expand(pieces) == expand(want)
         assert all(0 < v <= steps * STEP for _, _, v in pieces) and to == tier
@@ -89,4 +93,99 @@ def test_work_list_copies_what_moved(lib, hidden, page, shuffle, chunk_pages):
                 assert v == STEP or (s + 16 * v, d + 16 * v) != (s1, d1)
         assert sorted(w for _, w in lists) == sorted(pool.pages(i) for i, _ in some
                                                      if any(t != tier for t, _ in before[i]))
+    pool.destroy()
+
+
+def joined(copies):
+    """Copies of vectors, by source, those that continue one another made one; nothing is copied to twice."""
+    out = []
+    for s, d, v in sorted(copies):
+        if out and out[-1][0] + 16 * out[-1][2] == s and out[-1][1] + 16 * out[-1][2] == d:
+            out[-1][2] += v
+        else:
+            out.append([s, d, v])
+    ends = sorted((d, d + 16 * v) for _, d, v in out)
+    assert all(a[1] <= b[0] for a, b in zip(ends, ends[1:]))
+    return out
+
+
+LONG = 8 << 20
+
+
+@pytest.mark.parametrize("hidden,page", [(8192, 64), (8192, 16), (1024, 4096)])      # 1 MiB, 256 KiB and 8 MiB pages
+@pytest.mark.parametrize("shuffle,chunk", [(0, 0), (0, 20 << 20), (3, 0)])
+def test_long_runs_are_copies(lib, hidden, page, shuffle, chunk):
+    rng = np.random.default_rng([hidden, page, shuffle, chunk])
+    pb = 2 * hidden * page
+    pages = (96 << 20) // pb
+    chunk_pages = max(1, (chunk or 1 << 30) // pb)
+    pool = Pool(lib, pages, pages, hidden, page, chunk, shuffle)
+    samples, left, vpr = [], pages, hidden // 8
+    while left > 0 and len(samples) < 8:
+        n = min(left, int(rng.integers(1, max(2, (20 << 20) // pb))))
+        rows = n * page - int(rng.integers(0, 2)) * int(rng.integers(0, page))
+        samples.append((pool.write(2, rows, S1)[1], rows))
+        left -= n
+    seen = 0
+    for round_ in range(6):
+        tier = (round_ + 1) % 2
+        some = samples if round_ < 2 else [samples[i] for i in rng.permutation(len(samples))[:4]]
+        before = {i: pool.frames(i) for i, _ in some}
+        lib.stub_clear()
+        assert pool.migrate([i for i, _ in some], tier, S1) == 0
+        want = [(a, b, min(page, n - k * page) * vpr) for i, n in some
+                for k, ((t0, a), (_, b)) in enumerate(zip(before[i], pool.frames(i))) if t0 != tier]
+        if not want:
+            continue
+        pieces, _, _, _, _ = work_list(lib)
+        copies = [(s, d, n // 16) for s, d, n in pool.copies()]
+        assert joined(pieces + copies) == joined(want)
+        seen += len(copies)
+        # the runs: pages in the order they are moved, each continuing the last on both sides
+        starts = chunk_starts(pool, pages, chunk_pages)
+        runs = []
+        for s, d, v in want:
+            if (runs and runs[-1][0] + 16 * runs[-1][2] == s and runs[-1][1] + 16 * runs[-1][2] == d
+                    and s not in starts and d not in starts):
+                runs[-1][2] += v
+            else:
+                runs.append([s, d, v])
+        assert [tuple(r) for r in runs if 16 * r[2] >= LONG] == copies
+        log = pool.log()
+        assert log[-1].startswith("launch") and sum(l.startswith("launch") for l in log) == 1
+    assert seen > 0 or shuffle
+    pool.destroy()
+
+
+def chunk_starts(pool, pages, chunk_pages):
+    """Addresses of the first pages of the backing chunks (frames in order only where they are not shuffled)."""
+    out = set()
+    rs, ss, pb = (C.c_uint64 * 2)(), (C.c_uint64 * 2)(), C.c_int64()
+    assert pool.lib.pool_layout(pool.p, rs, ss, pb) == 0
+    for t in range(2):
+        at = []
+        for k in range(pages):
+            tier, phys = C.c_int32(), C.c_uint64()
+            assert pool.lib.pool_translate(pool.p, ss[t] + k * pb.value, tier, phys) == 0
+            at.append(phys.value)
+        if sorted(at) == at or chunk_pages < pages:
+            out |= {at[k] for k in range(0, pages, chunk_pages)}
+        else:
+            out.add(min(at))
+    return out
+
+
+def test_a_failed_copy_gives_the_pages_back_after_a_wait(lib):
+    pool = Pool(lib, 24, 24, 8192, 64)
+    i = pool.write(2, 20 * 64, S1)[1]
+    pool.lib.pool_reclaim(pool.p, 1, None)
+    before, frames = pool.stats(), pool.frames(i)
+    lib.stub_copy(hr.INVALID_VALUE)
+    pool.log()
+    assert pool.migrate([i], 1, S1) == -6
+    lib.stub_copy(0)
+    log = pool.log()
+    assert f"copy {S1}" in log and f"stream_sync {S1}" in log and not any("launch" in l for l in log)
+    assert pool.stats() == before and pool.frames(i) == frames
+    assert pool.migrate([i], 1, S1) == 0
     pool.destroy()
