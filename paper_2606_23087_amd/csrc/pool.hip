@@ -1133,35 +1133,15 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
       unreserve();
       return st;
     }
-    // Staging: the work list of the migration kernel (the samples' new page
-    // lists, then the pieces to copy, of at most `most` vectors each).
-    const int64_t page_vecs = p->pb / 16;
-    const int64_t most = page_vecs < fp::kMigratePageSteps * (int64_t)fp::kMigrateVecs
-                             ? (int64_t)fp::kMigrateVecs
-                             : std::min(page_vecs, fp::kMigratePieceVecs);
-    size_t at = sizeof(fp::MigrateList) * recs.size();
-    size_t pieces_at = at;
-    for (SampleRec* r : recs) pieces_at += (size_t)align16(8 * (int64_t)r->pages.size());
-    const size_t stage_bytes = pieces_at + sizeof(fp::MigratePiece) * (size_t)(need * ((page_vecs + most - 1) / most));
-    Stage* sg = nullptr;
-    st = stage_acquire(p, stage_bytes, 0, &sg);
-    int32_t ev = -1;
-    if (st == FP_OK && p->events.acquire(&ev) != hipSuccess) st = fail(FP_EHIP, "migration event");
-    if (st != FP_OK) {
-      unreserve();
-      return st;
-    }
-    // From here on nothing fails half-way but a copy or the launch: take the pages.
+    // What goes where: each page to the next page of the tier's free stack, in
+    // runs of pages that are adjacent in both tiers, each inside one backing
+    // chunk (one allocation) on either side.
+    struct Run { uint64_t src, dst; int64_t vecs; };
+    std::vector<Run> runs;
     std::vector<std::vector<uint64_t>> new_pages(recs.size());
     std::vector<std::vector<uint64_t>> old_pages(recs.size());
     const int64_t P = p->cfg.page_tokens;
     auto frame = [&](uint64_t gva) { return p->pte[(size_t)page_number(p, gva)] & fp::PTE_ADDR_MASK; };
-    fp::MigrateList* list = reinterpret_cast<fp::MigrateList*>(sg->host);
-    fp::MigratePiece* const pieces = reinterpret_cast<fp::MigratePiece*>(sg->host + pieces_at);
-    // Runs of pages that are adjacent in both tiers, each inside one backing
-    // chunk (one allocation) on either side.
-    struct Run { uint64_t src, dst; int64_t vecs; };
-    std::vector<Run> runs;
     auto add_copy = [&](uint64_t src, uint64_t dst, int64_t vecs) {
       if (!runs.empty()) {
         Run& last = runs.back();
@@ -1174,21 +1154,48 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
       }
       runs.push_back(Run{src, dst, vecs});
     };
+    size_t top = p->stack[tier].size();
     for (size_t j = 0; j < recs.size(); ++j) {
-      SampleRec& r = *recs[j];
+      const SampleRec& r = *recs[j];
       new_pages[j] = r.pages;
       for (int32_t k : moving[j]) {
-        const int64_t i = p->stack[tier].back();
-        p->stack[tier].pop_back();
-        p->used[tier][i] = 1;
-        p->n_free[tier] -= 1;
-        const uint64_t gva = p->page_gva(tier, i);
-        const int64_t rows = std::min<int64_t>(P, r.n_vis - (int64_t)k * P);
-        add_copy(frame(r.pages[(size_t)k]), frame(gva), rows * (p->rb / 16));
-        old_pages[j].push_back(r.pages[(size_t)k]);
-        new_pages[j][(size_t)k] = gva;
+        const uint64_t from = r.pages[(size_t)k], to = p->page_gva(tier, p->stack[tier][--top]);
+        add_copy(frame(from), frame(to), std::min<int64_t>(P, r.n_vis - (int64_t)k * P) * (p->rb / 16));
+        old_pages[j].push_back(from);
+        new_pages[j][(size_t)k] = to;
       }
-      *list++ = fp::MigrateList{(int64_t)at, pl_off[j], (int32_t)new_pages[j].size(), r.slot, 0};
+    }
+    // Staging: the work list of the migration kernel (the samples' new page
+    // lists, then the pieces to copy, of at most `most` vectors each). A long run
+    // is one copy by the DMA engines instead of pieces.
+    auto by_copy = [](const Run& run) { return 16 * run.vecs >= fp::kMigrateCopyBytes; };
+    const int64_t page_vecs = p->pb / 16;
+    const int64_t most = page_vecs < fp::kMigratePageSteps * (int64_t)fp::kMigrateVecs
+                             ? (int64_t)fp::kMigrateVecs
+                             : std::min(page_vecs, fp::kMigratePieceVecs);
+    size_t at = sizeof(fp::MigrateList) * recs.size();
+    size_t pieces_at = at;
+    for (SampleRec* r : recs) pieces_at += (size_t)align16(8 * (int64_t)r->pages.size());
+    size_t n_pieces = 0;
+    for (const Run& run : runs)
+      if (!by_copy(run)) n_pieces += (size_t)((run.vecs + most - 1) / most);
+    Stage* sg = nullptr;
+    st = stage_acquire(p, pieces_at + sizeof(fp::MigratePiece) * n_pieces, 0, &sg);
+    int32_t ev = -1;
+    if (st == FP_OK && p->events.acquire(&ev) != hipSuccess) st = fail(FP_EHIP, "migration event");
+    if (st != FP_OK) {
+      unreserve();
+      return st;
+    }
+    // From here on nothing fails half-way but a copy or the launch: take the pages.
+    for (int64_t q = 0; q < need; ++q) {
+      p->used[tier][p->stack[tier].back()] = 1;
+      p->stack[tier].pop_back();
+    }
+    p->n_free[tier] -= need;
+    fp::MigrateList* list = reinterpret_cast<fp::MigrateList*>(sg->host);
+    for (size_t j = 0; j < recs.size(); ++j) {
+      *list++ = fp::MigrateList{(int64_t)at, pl_off[j], (int32_t)new_pages[j].size(), recs[j]->slot, 0};
       std::memcpy(sg->host + at, new_pages[j].data(), 8 * new_pages[j].size());
       at += (size_t)align16(8 * (int64_t)new_pages[j].size());
     }
@@ -1197,24 +1204,22 @@ fp_status pool_migrate(fp_pool* p, const uint64_t* sample_ids, int32_t n, int32_
     ma.meta = p->meta_dev;
     ma.desc_table = p->desc_dev;
     ma.pieces_at = (int64_t)pieces_at;
-    // A long run is one copy by the DMA engines, the others are cut into the
-    // kernel's pieces (no more of them than of each page on its own).
+    ma.n_pieces = (uint32_t)n_pieces;
+    ma.steps_per_piece = (uint32_t)((most + fp::kMigrateVecs - 1) / fp::kMigrateVecs);
+    ma.n_lists = (int32_t)recs.size();
+    ma.tier = tier;
+    fp::MigratePiece* piece = reinterpret_cast<fp::MigratePiece*>(sg->host + pieces_at);
     hipError_t e = hipSuccess;
-    uint32_t n_pieces = 0;
     for (const Run& run : runs) {
-      if (16 * run.vecs >= fp::kMigrateCopyBytes) {
+      if (by_copy(run)) {
         e = hipMemcpyAsync((void*)run.dst, (const void*)run.src, 16 * (size_t)run.vecs, hipMemcpyDefault, hs);
         if (e != hipSuccess) break;
         continue;
       }
       for (int64_t v = 0; v < run.vecs; v += most)
-        pieces[n_pieces++] = fp::MigratePiece{run.src + 16 * (uint64_t)v, run.dst + 16 * (uint64_t)v,
-                                              (uint32_t)std::min(run.vecs - v, most), 0, 0};
+        *piece++ = fp::MigratePiece{run.src + 16 * (uint64_t)v, run.dst + 16 * (uint64_t)v,
+                                    (uint32_t)std::min(run.vecs - v, most), 0, 0};
     }
-    ma.n_pieces = n_pieces;
-    ma.steps_per_piece = (uint32_t)((most + fp::kMigrateVecs - 1) / fp::kMigrateVecs);
-    ma.n_lists = (int32_t)recs.size();
-    ma.tier = tier;
     if (e == hipSuccess) e = fp::launch_migrate(ma, hs, p->events.ev[(size_t)ev]);
     if (e != hipSuccess) {
       st = fail_behind(hs, fail(FP_EHIP, "migration: %s", hipGetErrorString(e)));

@@ -153,6 +153,7 @@ def test_long_runs_are_copies(lib, hidden, page, shuffle, chunk):
         assert [tuple(r) for r in runs if 16 * r[2] >= LONG] == copies
         log = pool.log()
         assert log[-1].startswith("launch") and sum(l.startswith("launch") for l in log) == 1
+        assert not any("malloc" in l for l in log)
     assert seen > 0 or shuffle
     pool.destroy()
 
@@ -173,6 +174,19 @@ def chunk_starts(pool, pages, chunk_pages):
         else:
             out.add(min(at))
     return out
+
+
+def test_the_work_list_takes_the_room_it_needs(lib):
+    """The staging of 6000 pages of 28 KiB: 8 bytes each and 32 a piece, 7 pieces each in a random order; where they are
+    adjacent they are copies by the runtime."""
+    for shuffle, most in ((0, 0), (5, 6000 * (8 + 7 * 32) + 4096)):
+        pool = Pool(lib, 6000, 6000, 1024, 14, 0, shuffle)
+        ids = [pool.write(1, 14 * 1000, S1)[1] for _ in range(6)]
+        pool.log()
+        assert pool.migrate(ids, 1, S1) == 0
+        taken = [int(l.split()[1]) for l in pool.log() if l.startswith("host_malloc")]
+        assert sum(taken) <= most and len(taken) == (1 if shuffle else 0)
+        pool.destroy()
 
 
 def test_a_failed_copy_gives_the_pages_back_after_a_wait(lib):
