@@ -882,6 +882,7 @@ fp_status pool_write_sample(fp_pool* p, const int32_t* text_ids, int32_t n_text,
                     p->cfg.device);
       vis_dev = (const uint8_t*)attr.devicePointer;
     }
+    // Never empty: a sample has a row, so a text id or a page.
     const int64_t meta_len = align16(8 * n_pages) + align16(8ll * n_img) + align16(4ll * n_text);
     int64_t meta_off = 0;
     SampleRec rec;
@@ -893,11 +894,11 @@ fp_status pool_write_sample(fp_pool* p, const int32_t* text_ids, int32_t n_text,
       st = FP_OK;
       if (p->free_slots.empty()) {
         st = fail(FP_ENOMEM, "all %lld sample slots in use", (long long)p->cfg.max_samples);
-      } else if (meta_len > 0 && (meta_off = p->meta.alloc(meta_len)) < 0) {
+      } else if ((meta_off = p->meta.alloc(meta_len)) < 0) {
         st = fail(FP_ENOMEM, "metadata arena full (%lld bytes wanted)", (long long)meta_len);
       } else {
         st = alloc_pages(p, n_pages, page_tier_wish, &rec.pages);
-        if (st != FP_OK && meta_len > 0) p->meta.release(meta_off, meta_len);
+        if (st != FP_OK) p->meta.release(meta_off, meta_len);
       }
       if (st == FP_OK) break;
       if (attempt > 0 || p->deferred.empty()) return st;
@@ -906,7 +907,7 @@ fp_status pool_write_sample(fp_pool* p, const int32_t* text_ids, int32_t n_text,
     auto rollback = [&](fp_status s) {
       std::string keep = t_err;
       release_pages(p, rec.pages);
-      if (meta_len > 0) p->meta.release(meta_off, meta_len);
+      p->meta.release(meta_off, meta_len);
       t_err = keep;
       return s;
     };
@@ -924,23 +925,21 @@ fp_status pool_write_sample(fp_pool* p, const int32_t* text_ids, int32_t n_text,
     // nothing else is enqueued, and its completion is both the sample's write
     // event and the staging buffer's.
     Stage* s = nullptr;
-    if (meta_len > 0) {
-      st = stage_acquire(p, (size_t)meta_len, 0, &s);
-      if (st != FP_OK) return rollback(st);
-      std::memcpy(s->host, rec.pages.data(), 8 * (size_t)n_pages);
-      int32_t* img = (int32_t*)(s->host + (d.img_off - meta_off));
-      for (int32_t j = 0; j < n_img; ++j) {
-        img[2 * j] = img_pos[j];
-        img[2 * j + 1] = img_ntok[j];
-      }
-      if (n_text) std::memcpy(s->host + (d.text_off - meta_off), text_ids, 4 * (size_t)n_text);
+    st = stage_acquire(p, (size_t)meta_len, 0, &s);
+    if (st != FP_OK) return rollback(st);
+    std::memcpy(s->host, rec.pages.data(), 8 * (size_t)n_pages);
+    int32_t* img = (int32_t*)(s->host + (d.img_off - meta_off));
+    for (int32_t j = 0; j < n_img; ++j) {
+      img[2 * j] = img_pos[j];
+      img[2 * j + 1] = img_ntok[j];
     }
+    if (n_text) std::memcpy(s->host + (d.text_off - meta_off), text_ids, 4 * (size_t)n_text);
     const int32_t slot = p->free_slots.back();
     fp::WritePlan w;
     fp::WriteArgs& wa = w.a;
     wa.desc = d;
     wa.desc_table = p->desc_dev;
-    wa.stage = s ? s->host_dev : nullptr;
+    wa.stage = s->host_dev;
     wa.meta = p->meta_dev + meta_off;
     wa.pte = p->pte_dev;
     w.vis = vis_dev;
@@ -976,10 +975,8 @@ fp_status pool_write_sample(fp_pool* p, const int32_t* text_ids, int32_t n_text,
       p->events.unref(ev);
       return rollback(st);
     }
-    if (s) {
-      p->events.ref(ev);
-      s->shared = ev;
-    }
+    p->events.ref(ev);
+    s->shared = ev;
     rec.written = ev;
     rec.write_stream = stream;
     p->free_slots.pop_back();
