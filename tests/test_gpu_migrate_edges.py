@@ -1,8 +1,7 @@
-"""The migration kernel at the edges of its steps (1024 vectors): pages of one
-vector, of less than a step, of whole steps, of steps and a remainder, with the
-last page of a sample partial; one page and more pages than workgroups; page
-lists longer than a workgroup; both directions, partly migrated samples among
-them. Every byte of both tiers' caller-owned memory is checked after each
+"""The migration kernel over page sizes of one vector to many steps (of 256
+vectors), with and without a remainder, with the last page of a sample partial;
+one page and more pages than workgroups; page lists longer than a step; both
+directions, partly migrated samples among them, in shuffled frames. Every byte of both tiers' caller-owned memory is checked after each
 migration: moved rows at their new frames, everything else as it was; then a
 pack against the definitional pack checks the uploaded page lists.
 """
@@ -36,8 +35,8 @@ CASES = [
     (8, 1, [1]),
     (8, 1, [300, 2]),                # a page list of more than 256 words, one-vector pages
     (8, 1000, [2500, 1, 999]),       # pages of 1000 vectors
-    (8, 1024, [3000]),               # one step a page
-    (8, 1025, [3076, 1025]),         # a step and one vector
+    (8, 1024, [3000]),               # four steps a page
+    (8, 1025, [3076, 1025]),         # and one vector more
     (256, 16, [5, 64, 0, 33]),
     (3584, 37, [151, 37]),
     (4096, 64, [64, 130, 1, 200]),

@@ -328,12 +328,11 @@ def _head_specs(rng, n, max_img, vocab):
 def test_chunk_head_shapes(fp, hidden, page_tokens, pack_cus):
     """Row resolution at every chunk shape: many rows per chunk (small H,
     one row per lane) down to chunks inside one row (large H); page sizes
-    that are not powers of two; 17..32 samples with an inline run table,
-    samples with eleven images, empty images and adjacent images (merged
-    runs), the 32-sample and 160-run limits of the inline table and
-    microbatches just past them (staged table), the 8-sample and 24-run
-    limits of the compact kernel arguments and one past each, and 64 or
-    more samples. pack_cus=1 sizes the chunk
+    that are not powers of two; 17..32 samples, samples with eleven images,
+    empty images and adjacent images (merged runs), 64 or more samples; run
+    tables just inside and just past the compact kernel arguments, the general
+    ones with 64 buckets and with 16 (a device copy past those), with many
+    runs a sample and with few. pack_cus=1 sizes the chunk
     geometry for one compute unit, so these small packs also take full
     chunks and both shrinking tail stages; with the device's count they are
     all in the last stage."""
@@ -358,7 +357,7 @@ def test_chunk_head_shapes(fp, hidden, page_tokens, pack_cus):
         r160 = int(np.searchsorted(runs, 160, side="right"))     # first r160 samples form <= 160 runs
         assert runs[r160 - 1] <= 160 < runs[r160] and r160 < 32
         assert runs[101] - runs[69] <= 160                         # samples 70..101 fit the inline table
-        # the compact kernel arguments' limits (8 samples, 24 runs) and one past each
+        # 8 samples and 24 runs, and one past each
         rn = [_runs(s) for s in specs]
         at24 = next([i, j] for i in range(70) for j in range(i + 1, 70) if rn[i] + rn[j] == 24)
         at25 = next([i, j] for i in range(70) for j in range(i + 1, 70) if rn[i] + rn[j] == 25)
@@ -366,6 +365,14 @@ def test_chunk_head_shapes(fp, hidden, page_tokens, pack_cus):
         groups = [list(range(17)), list(range(r160)), list(range(r160 + 1)),
                   list(range(70, 102)), list(range(70, 103)), list(range(70, 134)), list(range(70)),
                   [11, 23, 11, 35, 140 - 1], list(range(70, 78)), list(range(70, 79)), at24, at25, [11]]
+        # on both sides of each limit of the run table: 704 bytes with 16 buckets, 3840 with 64 and with 16
+        def size_of(g, buckets):
+            return (4 * len(g) + 15) // 16 * 16 + 16 * sum(rn[i] for i in g) + 18 * buckets
+        for order in (list(range(140)), list(range(70, 140)) + list(range(70))):
+            for room, buckets in ((704, 16), (3840, 64), (3840, 16)):
+                k = max(k for k in range(1, 141) if size_of(order[:k], buckets) <= room)
+                assert k < 140 and size_of(order[:k], buckets) <= room < size_of(order[:k + 1], buckets)
+                groups += [order[:k], order[:k + 1]]
         for g in groups:
             say(f"  group of {len(g)} samples, {sum(_runs(specs[i]) for i in g)} runs")
             n, mx = w.pack([w.ids[i] for i in g], out, cu, pos)

@@ -5,8 +5,10 @@
   two wait states gfx940-class parts need before a VALU instruction may
   overwrite the store's data registers (the compiler cannot see into asm,
   so it does not insert them).
-- The pack kernels spill nothing to scratch and stay within the registers
-  that keep 8 waves per SIMD resident.
+- The pack kernels stay within the registers that keep 8 waves per SIMD
+  resident, and no kernel uses scratch. Besides its cost, a kernel whose
+  arguments were copied there would read its run table or page list at private
+  addresses taken for global ones.
 - The pack kernels' leading scalar arguments (13 dwords) arrive preloaded in
   scalar registers, and the first loads of the row lookup (the bucket's run and
   index entry) are issued before the wait for the other kernel arguments, so the two are in
@@ -72,6 +74,16 @@ def test_pack_kernels_keep_full_occupancy(isa):
         scratch = int(re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", meta).group(1))
         assert scratch == 0, name
         assert vgpr <= 64, (name, vgpr)         # 512 VGPRs per lane / 8 waves
+
+
+@pytest.mark.parametrize("kernel,forms", [("k_pack", 4), ("k_write", 4), ("k_migrate", 2), ("k_cost", 1), ("k_copy", 2),
+                                          ("k_gather", 2)])
+def test_no_kernel_uses_scratch(isa, kernel, forms):
+    found = {k: v for k, v in _kernels(isa).items() if kernel in k}
+    assert len(found) == forms
+    for name, (lines, meta) in found.items():
+        assert int(re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", meta).group(1)) == 0, name
+        assert not any("scratch_" in l for l in lines), name
 
 
 def test_pack_kernels_preload_their_head_arguments(isa):

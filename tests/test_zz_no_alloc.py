@@ -41,10 +41,21 @@ def _outs(rows, hidden, n):
     return out, cu, pos
 
 
+def _runs(spec):
+    """Stretches of text rows or of image rows of one sample."""
+    n, ti, in_image = 0, 0, False
+    for p, t in zip(spec.img_pos.tolist(), spec.img_ntok.tolist()):
+        if p > ti:
+            n, ti, in_image = n + 1, p, False
+        if t > 0 and not in_image:
+            n, in_image = n + 1, True
+    return n + (spec.n_text > ti)
+
+
 def test_noalloc_pack_matches_pack(fp):
     cfg = scaled(CONFIGS["tiny"], hbm_pages=2000)
     seed = 5
-    specs = gen_samples(cfg, seed, count=48)
+    specs = gen_samples(cfg, seed, count=96)
     say(f"case no-alloc pack: H={cfg.hidden} P={cfg.page_tokens} samples={len(specs)}")
     pool = fp.pool_create(hidden=cfg.hidden, page_tokens=cfg.page_tokens, hbm_pages=cfg.hbm_pages,
                           vocab=cfg.vocab, alloc="scatter", pack_cus=2)
@@ -55,7 +66,10 @@ def test_noalloc_pack_matches_pack(fp):
         ids = [fp.pool_write_sample(pool, s.text_ids, s.img_pos, s.img_ntok, to_dev(v) if s.n_vis else None)
                for s, v in zip(specs, vis)]
         torch.cuda.synchronize()
-        groups = [list(range(0, 44)), list(range(3, 40)), list(range(7, 12))]   # 44 and 37 samples: scratch; 5: arguments
+        groups = [list(range(0, 90)), list(range(3, 83)), list(range(7, 12))]   # 90 and 80 samples: scratch; 5: arguments
+        # 4 bytes a sample, 16 a run and at least 288 of index travel in 3840 bytes of kernel arguments
+        sizes = [(4 * len(g) + 15) // 16 * 16 + 16 * sum(_runs(specs[i]) for i in g) + 288 for g in groups]
+        assert sizes[0] > sizes[1] > 3840 >= sizes[2]
         rows = [sum(specs[i].length for i in g) for g in groups]
         big = max(rows) + 16
         a = [_outs(big, cfg.hidden, len(g)) for g in groups]
