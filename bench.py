@@ -548,7 +548,7 @@ def concurrent_bench(args, cfg, w, mbs, spec_of, outs, pack_stream) -> dict:
 def prefetch_bench(args, cfg, w, mbs, spec_of, outs, pack_stream) -> dict:
     """Tiered pool: pack every microbatch reading host-tier pages zero-copy over
     PCIe, then the same packs with each microbatch's host-tier pages first
-    promoted into HBM by DMA copies on a copy stream (pool_migrate), the
+    promoted into HBM on a copy stream (pool_migrate), the
     migration of microbatch j+1 overlapping the pack of microbatch j, then the
     packs again once everything sits in HBM."""
     import torch

@@ -392,20 +392,6 @@ __device__ __forceinline__ void chunk_range(int bx, int32_t g0, int32_t g1, int3
   }
 }
 
-// Producer write (Sec. 3.2): the first n_meta workgroups copy the sample's
-// metadata block from pinned host memory into the arena and publish the
-// descriptor; the others move the sample's contiguous visual rows into its
-// pages, one chunk each, with the pack's chunk geometry. A thread's rows do
-// not depend on where they go, so their loads are issued first and the
-// destinations (visual row -> page number -> page-table entry -> row in the
-// physical page) are resolved while they are in flight, one row per wave with
-// scalar loads or, for chunks of many short rows, one row per lane.
-//
-// Small writes are bound by their launches: the metadata as a copy of its own
-// ahead of the kernel and an event after each cost 8 us of host time and 6 us
-// of GPU time per write. A sample of 31 MB read and written takes 6.7 us in
-// this kernel (4.7 TB/s; 7.8 us with chunks of one size and the loads after
-// the walk), one of 64 rows of 512 bytes 2.3 us (3.4 us, and a 2.2 us copy).
 // Rows [r0, r0 + rows) of a write: their destinations, into LDS.
 template <class Args>
 __device__ __forceinline__ void write_rows(const Args& a, int r0, int rows, uint64_t* s_dst, int tid) {
@@ -462,6 +448,20 @@ __device__ __forceinline__ void write_chunk(const Args& a, const uint8_t* vis, u
   }
 }
 
+// Producer write (Sec. 3.2): the first n_meta workgroups copy the sample's
+// metadata block from pinned host memory into the arena and publish the
+// descriptor; the others move the sample's contiguous visual rows into its
+// pages, one chunk each, with the pack's chunk geometry. A thread's rows do
+// not depend on where they go, so their loads are issued first and the
+// destinations (visual row -> page number -> page-table entry -> row in the
+// physical page) are resolved while they are in flight, one row per wave with
+// scalar loads or, for chunks of many short rows, one row per lane.
+//
+// Small writes are bound by their launches: the metadata as a copy of its own
+// ahead of the kernel and an event after each cost 8 us of host time and 6 us
+// of GPU time per write. A sample of 31 MB read and written takes 6.7 us in
+// this kernel (4.7 TB/s; 7.8 us with chunks of one size and the loads after
+// the walk), one of 64 rows of 512 bytes 2.3 us (3.4 us, and a 2.2 us copy).
 template <int VPT, class Args>
 __global__ __launch_bounds__(kPackBlock) void k_write(int32_t g0, int32_t g1, int32_t t1, int32_t t2,
                                                        uint64_t div_mul, const uint8_t* vis, int32_t div_shift,
