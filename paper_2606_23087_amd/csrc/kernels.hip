@@ -598,7 +598,7 @@ __global__ __launch_bounds__(kMigrateBlock) void k_migrate(MigrateArgs a) {
 
 // One thread per sample. Bound by latency: the host waits for the launch, a
 // dependent pair of loads and the stores to pinned memory, 5 to 6 us in all
-// beside the 2.6 us of the launch.
+// beside the 3.6 us of the launch; the kernel itself takes 2.2 us over 411 samples.
 __global__ __launch_bounds__(kBlock) void k_cost(CostArgs a) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i < a.n) {

@@ -1324,7 +1324,7 @@ fp_status plan_microbatches(fp_pool* p, const uint64_t* sample_ids, int32_t n, i
       // long slot lists from it): no copy kernels run beside the packs of
       // other streams. The wait is for the launch's own stop event, which
       // returns 2.7 us sooner than the stream's synchronisation; the staging
-      // buffer is free with it. A plan of 430 samples into 64 microbatches
+      // buffer is free with it. A plan of 411 samples into 64 microbatches
       // takes 26.7 us, of which the check of the list is next to nothing (a hash
       // set of the ids, filled while the kernel ran, made it 31.8).
       const size_t slot_bytes = align16(4ll * n);
