@@ -1,7 +1,7 @@
 """The library's host code on a stand-in HIP runtime (CPU only).
 
 ``build`` compiles the library's own sources for the host alone, links them
-with tests/host_runtime/stub_hip.cpp in place of the HIP runtime, and returns
+with tests/hip_stub/stub_hip.cpp in place of the HIP runtime, and returns
 the result as a ctypes library with the prototypes of the bindings. Its
 kernels are not run; what the host code enqueues, waits for and gives back is
 what the tests look at.
@@ -46,7 +46,7 @@ def build(tmp, csrc=CSRC):
         objs.append(o)
     stub = os.path.join(str(tmp), "stub.o")
     _run(["g++", "-std=c++17", "-O1", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
-          "-c", os.path.join(HERE, "host_runtime", "stub_hip.cpp"), "-o", stub])
+          "-c", os.path.join(HERE, "hip_stub", "stub_hip.cpp"), "-o", stub])
     so = os.path.join(str(tmp), "libflowpool_host.so")
     _run(["g++", "-shared", "-Wl,-Bsymbolic", *defs, *objs, stub, "-o", so])
     lib = C.CDLL(so)
